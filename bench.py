@@ -94,19 +94,6 @@ def profiled_traffic(entry):
     return None
 
 
-def sap_kernel_name(cfg, prec):
-    """The SAP half-sweep kernel the library launches for this workload: the pair form for
-    FP16 links and clover with at least 256 domains of each colour and 256-site domains,
-    the split-parity form otherwise (SAPDD_SAP_KERNEL=pair/split forces one)."""
-    force = os.environ.get("SAPDD_SAP_KERNEL")
-    ndom = int(np.prod(cfg["dims"])) // int(np.prod(cfg["block"]))
-    pair = prec in ("f16", "f16l") and ndom // 2 >= 256
-    if force in ("pair", "split"):
-        pair = force == "pair"
-    pair = pair and int(np.prod(cfg["block"])) >= 256
-    return "sap_pair_kernel" if pair else "sap_half_kernel"
-
-
 def roofline_sap(prof, cfg, prec, nmr):
     """Roofline of the SAP half-sweep from the HIP-event times of the timed steps: flops
     and algorithmic bytes per launch (one colour, every right-hand side), both roofs, and
@@ -123,7 +110,7 @@ def roofline_sap(prof, cfg, prec, nmr):
     byts = pm.sap_half_bytes(cfg["block"], prec, nrhs) * V / 2
     ar = "f64" if prec == "f64" else "f32"
     alu_peak, alu_pub = pm.ALU_PEAK_TFLOPS[ar], pm.ALU_PEAK_PUBLISHED_TFLOPS[ar]
-    kname = sap_kernel_name(cfg, prec)
+    kname = "sap_kernel"
     traffic = profiled_traffic(f"{kname} {'x'.join(map(str, cfg['dims']))} {'x'.join(map(str, cfg['block']))} "
                                f"{prec} nrhs {nrhs}")
     t_alu = flops / (alu_peak * 1e12)

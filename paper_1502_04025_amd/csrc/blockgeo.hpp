@@ -2,9 +2,9 @@
 // block, and the in-block hopping term evaluated through LDS.
 //
 // One workgroup owns one block (the GPU counterpart of the paper's one-domain-per-core
-// assignment, Sec. 3.3/3.5); thread tid < Vbh is the even site with half index tid and
-// thread Vbh + s the odd site s, so the two parities occupy separate waves whenever
-// Vbh >= 64.
+// assignment, Sec. 3.3/3.5). In the block operator thread tid < Vbh is the even site with
+// half index tid and thread Vbh + s the odd site s, so the two parities occupy separate
+// waves whenever Vbh >= 64; the Schwarz kernel has its own thread layout.
 #pragma once
 #include <utility>
 
@@ -24,8 +24,6 @@ template <int BX, int BY, int BZ, int BT> struct Blk {
     static constexpr int Vb = BX * BY * BZ * BT;
     static constexpr int Vbh = Vb / 2;
     static constexpr int NT = Vb;                         // threads per workgroup
-    static constexpr int W = NT < 64 ? NT : 64;           // lanes used per wave
-    static constexpr int NW = (NT + 63) / 64;             // waves per workgroup
     __device__ static constexpr int ext(int mu) { return mu == 0 ? BX : mu == 1 ? BY : mu == 2 ? BZ : BT; }
 };
 
@@ -62,12 +60,9 @@ template <class BK> __device__ __forceinline__ SiteInfo site_info(int tid) {
     return si;
 }
 
-// The four forward links of a thread's own site, either held in registers (as the
-// storage-precision 16-byte vectors they were loaded in, converted on use) or re-read
-// from global memory on every use.
-template <class S, class R, bool CACHE> struct SiteLinks;
-
-template <class S, class R> struct SiteLinks<S, R, true> {
+// The four forward links of a thread's own site, held in registers as the
+// storage-precision 16-byte vectors they were loaded in and converted on use.
+template <class S, class R> struct SiteLinks {
     typedef typename Vec<S>::type VT;
     static constexpr int W = Vec<S>::W;
     VT u[72 / W];
@@ -89,29 +84,6 @@ template <class S, class R> struct SiteLinks<S, R, true> {
             if constexpr (Storage<S>::scaled) out[k] = (R)(float)u[q / W][q % W];
             else out[k] = (R)u[q / W][q % W];
         }
-    }
-    __device__ __forceinline__ R scale() const {
-        if constexpr (Storage<S>::scaled) return sc;
-        else return (R)1;
-    }
-};
-
-template <class S, class R> struct SiteLinks<S, R, false> {
-    const S *base;
-    R sc;
-    int64_t bp;
-    int s, Vbh;
-    __device__ __forceinline__ void init(const S *__restrict__ b, const float *__restrict__ scl, int64_t bp_, int s_,
-                                         int vbh) {
-        base = b;
-        bp = bp_;
-        s = s_;
-        Vbh = vbh;
-        sc = site_scale<R, S>(scl, bp, s, Vbh);
-    }
-    // Link MU without the FP16 site scale (see scale()).
-    template <int MU> __device__ __forceinline__ void get(R out[18]) const {
-        load_reals<R, 72, 18 * MU, 18, S, true>(base, nullptr, bp, s, Vbh, out);
     }
     __device__ __forceinline__ R scale() const {
         if constexpr (Storage<S>::scaled) return sc;
@@ -181,39 +153,6 @@ __device__ __forceinline__ void clover_mul(const XR &X, const R (&in)[24], R (&o
     }
 }
 
-// The clover of a thread's own site, held in registers for the whole kernel or re-read
-// (from the L1/L2 caches) at every use.
-template <class S, class R, bool CACHE> struct SiteClover;
-
-template <class S, class R> struct SiteClover<S, R, true> {
-    CloverRegs<S, R> c;
-    __device__ __forceinline__ void init(const S *__restrict__ base, const float *__restrict__ scale, int64_t bp,
-                                         int s, int Vbh) {
-        c.load(base, scale, bp, s, Vbh);
-    }
-    __device__ __forceinline__ void mul(const R (&in)[24], R (&out)[24], R kx) const { clover_mul(c, in, out, kx); }
-};
-
-template <class S, class R> struct SiteClover<S, R, false> {
-    const S *base;
-    const float *scale;
-    int64_t bp;
-    int s, Vbh;
-    __device__ __forceinline__ void init(const S *__restrict__ b, const float *__restrict__ sc, int64_t bp_, int s_,
-                                         int vbh) {
-        base = b;
-        scale = sc;
-        bp = bp_;
-        s = s_;
-        Vbh = vbh;
-    }
-    __device__ __forceinline__ void mul(const R (&in)[24], R (&out)[24], R kx) const {
-        CloverRegs<S, R> c;
-        c.load(base, scale, bp, s, Vbh);
-        clover_mul(c, in, out, kx);
-    }
-};
-
 // In-block hopping term between the two parities, via LDS.
 //   Threads of parity `src` supply `in`. Threads of the other parity receive
 //   out = sum_mu [ (1 - gamma_mu) U_mu(x) in(x + mu) + (1 + gamma_mu) U_mu(x - mu)^+ in(x - mu) ]
@@ -222,21 +161,13 @@ template <class S, class R> struct SiteClover<S, R, false> {
 // Source threads store their spinor (for the forward hops of their backward neighbours)
 // and, for every in-block forward neighbour, the transported half spinor
 // U_mu(x)^+ (1 + gamma_mu) in(x); the receiving threads then need only their own links.
-// Every thread of the workgroup must call this; it contains one barrier (two with a
-// single LDS buffer).
-//
-// BF (branch-free): every lane does the work of every direction. The face conditions
-// differ between the lanes of a wave, so a branch issues the work for the whole wave
-// anyway; without it the compiler schedules the four directions as one stream. Lanes
-// without the in-block forward neighbour write a slot nobody reads, and receivers without
-// the neighbour accumulate it with weight zero; every slot a receiver reads has been
-// written, so the zero weights only ever meet finite values. This loads the links of the
-// face sites too, which the operator does not need: the instruction-bound SAP kernels
-// use it, the memory-bound block operator does not.
-template <int MU, class BK, bool BF, class R, class LK>
+// Every thread of the workgroup must call this; it contains two barriers. Face sites skip
+// the hops that leave the block: their links are not loaded (the block operator, whose
+// kernels use this, is bound by memory).
+template <int MU, class BK, class R, class LK>
 __device__ __forceinline__ void push_dir(const SiteInfo &si, const LK &U, const R (&in)[24], R *__restrict__ hb) {
     constexpr int Vbh = BK::Vbh;
-    if (BF || (si.fin & (1u << MU))) {
+    if (si.fin & (1u << MU)) {
         R h[12], uh[12], u[18];
         project<MU, +1>(in, h);
         U.template get<MU>(u);
@@ -247,12 +178,11 @@ __device__ __forceinline__ void push_dir(const SiteInfo &si, const LK &U, const 
     }
 }
 
-template <int MU, class BK, bool BF, class R, class LK>
+template <int MU, class BK, class R, class LK>
 __device__ __forceinline__ void pull_dir(const SiteInfo &si, const LK &U, R (&out)[24], const R *__restrict__ sp,
                                          const R *__restrict__ hb) {
     constexpr int Vbh = BK::Vbh;
-    const bool f = (si.fin >> MU) & 1u, b = (si.bin >> MU) & 1u;
-    if (BF || f) {
+    if (si.fin >> MU & 1u) {
         R chi[24], h[12], uh[12], u[18];
         const int n = si.nbf[MU];
 #pragma unroll
@@ -260,61 +190,47 @@ __device__ __forceinline__ void pull_dir(const SiteInfo &si, const LK &U, R (&ou
         project<MU, -1>(chi, h);
         U.template get<MU>(u);
         su3_mul(u, h, uh);
-        accum_recon<MU, -1>(out, uh, f ? U.scale() : (R)0);
+        accum_recon<MU, -1>(out, uh, U.scale());
     }
-    if (BF || b) {
+    if (si.bin >> MU & 1u) {
         R uh[12];
         const int n = si.nbb[MU];
 #pragma unroll
         for (int k = 0; k < 12; ++k) uh[k] = hb[(MU * 12 + k) * Vbh + n];
-        accum_recon<MU, +1>(out, uh, b ? (R)1 : (R)0);
+        accum_recon<MU, +1>(out, uh, (R)1);
     }
 }
 
-// LDS exchange area of block_hop: NBUF buffers of (spinor + 4 transported half
-// spinors) per source site. With two buffers consecutive hops alternate between them
-// and each hop needs only its middle barrier: a thread can only start writing buffer i
-// again (hop n + 2) after passing hop n + 1's barrier, which every thread reaches only
-// after finishing its reads of hop n.
-template <class BK, class R, int WANT = 2> struct HopLds {
-    static constexpr int PER = 72 * BK::Vbh;  // reals per buffer: 24 (spinor) + 48 (half spinors)
-    static constexpr int NBUF = WANT == 2 && 2 * PER * (int)sizeof(R) <= 150 * 1024 ? 2 : 1;
-    R *base;
-    int cur;
-    __device__ __forceinline__ R *sp() const { return base + cur * PER; }
-    __device__ __forceinline__ R *hb() const { return base + cur * PER + 24 * BK::Vbh; }
+// Reals of LDS that block_hop needs: a spinor and four transported half spinors per source
+// site.
+template <class BK> struct HopLds {
+    static constexpr int PER = 72 * BK::Vbh;
 };
 
-// TAIL = false (one LDS buffer only): the caller guarantees a barrier between the
-// receivers' reads and the next hop's writes, and the trailing barrier is left out.
-template <class BK, bool TAIL = true, bool BF = false, class R, class LK, int WANT>
+template <class BK, class R, class LK>
 __device__ __forceinline__ void block_hop(int src, const SiteInfo &si, const LK &U, const R (&in)[24], R (&out)[24],
-                                          HopLds<BK, R, WANT> &lds) {
+                                          R *__restrict__ lds) {
     constexpr int Vbh = BK::Vbh;
-    R *__restrict__ sp = lds.sp();
-    R *__restrict__ hb = lds.hb();
+    R *__restrict__ sp = lds;
+    R *__restrict__ hb = lds + 24 * Vbh;
     if (si.p == src) {
 #pragma unroll
         for (int k = 0; k < 24; ++k) sp[k * Vbh + si.s] = in[k];
-        push_dir<0, BK, BF>(si, U, in, hb);
-        push_dir<1, BK, BF>(si, U, in, hb);
-        push_dir<2, BK, BF>(si, U, in, hb);
-        push_dir<3, BK, BF>(si, U, in, hb);
+        push_dir<0, BK>(si, U, in, hb);
+        push_dir<1, BK>(si, U, in, hb);
+        push_dir<2, BK>(si, U, in, hb);
+        push_dir<3, BK>(si, U, in, hb);
     }
     __syncthreads();
     if (si.p != src) {
 #pragma unroll
         for (int k = 0; k < 24; ++k) out[k] = 0;
-        pull_dir<0, BK, BF>(si, U, out, sp, hb);
-        pull_dir<1, BK, BF>(si, U, out, sp, hb);
-        pull_dir<2, BK, BF>(si, U, out, sp, hb);
-        pull_dir<3, BK, BF>(si, U, out, sp, hb);
+        pull_dir<0, BK>(si, U, out, sp, hb);
+        pull_dir<1, BK>(si, U, out, sp, hb);
+        pull_dir<2, BK>(si, U, out, sp, hb);
+        pull_dir<3, BK>(si, U, out, sp, hb);
     }
-    if constexpr (HopLds<BK, R, WANT>::NBUF == 2) {
-        lds.cur ^= 1;
-    } else if constexpr (TAIL) {
-        __syncthreads();  // one buffer: the next hop may only overwrite it after every read
-    }
+    __syncthreads();  // the next hop may only overwrite the buffer after every read
 }
 
 }  // namespace sapdd

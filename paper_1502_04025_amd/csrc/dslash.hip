@@ -230,8 +230,7 @@ __global__ __launch_bounds__(BK::NT) void dslash_block_kernel(Geom geo, CF<S> li
     constexpr int Vbh = BK::Vbh;
     // one LDS buffer: this memory-bound kernel gains more from occupancy than from the
     // barrier a second buffer would save
-    __shared__ R lds_hop[HopLds<BK, R, 1>::PER];
-    HopLds<BK, R, 1> lds{lds_hop, 0};
+    __shared__ R lds[HopLds<BK>::PER];
     const SiteInfo si = site_info<BK>(threadIdx.x);
     const int64_t b = blockIdx.x;
     const int rhs = blockIdx.y;
@@ -243,7 +242,7 @@ __global__ __launch_bounds__(BK::NT) void dslash_block_kernel(Geom geo, CF<S> li
     // (measured 4.71 -> 5.52 TB/s in FP32, 4.49 -> 4.80 TB/s in FP16 on 32^3x64). Issuing
     // the clover loads before the hops instead of after measured slower.
     constexpr bool NT = true;
-    SiteLinks<S, R, true> U;
+    SiteLinks<S, R> U;
     U.template init<NT>(links.data, links.scale, bp, si.s, Vbh);
     R psi[24], hop[24];
     load_site<R, 24, S, NT>(in.data + ioff, in.scale ? in.scale + soff : nullptr, bp, si.s, Vbh, psi);

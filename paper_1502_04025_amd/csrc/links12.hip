@@ -81,8 +81,7 @@ __global__ __launch_bounds__(BK::NT) void dslash_block12_kernel(Geom geo, const 
                                                                 const S *in, const float *inscale, S *out,
                                                                 float *outscale) {
     constexpr int Vbh = BK::Vbh;
-    __shared__ R lds_hop[HopLds<BK, R, 1>::PER];
-    HopLds<BK, R, 1> lds{lds_hop, 0};
+    __shared__ R lds[HopLds<BK>::PER];
     const SiteInfo si = site_info<BK>(threadIdx.x);
     const int64_t b = blockIdx.x;
     const int rhs = blockIdx.y;

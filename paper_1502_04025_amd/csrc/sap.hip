@@ -11,16 +11,46 @@
 //   3. adds delta to psi and keeps delta and the new even-site residual for the next
 //      half-sweep.
 // The block never leaves the workgroup during the MR iterations: spinors live in
-// registers and LDS, the in-block hops go through LDS (block_hop) and the MR inner
-// products are wave-shuffle plus LDS reductions in a fixed order (so results do not
-// depend on scheduling). Blocks of one colour share no site and no hop, so the gather
-// form (each block reads its neighbours, nobody writes into another block) is race free.
+// registers and LDS and the MR inner products are wave plus LDS reductions in a fixed
+// order (so results do not depend on scheduling). Blocks of one colour share no site and
+// no hop, so the gather form (each block reads its neighbours, nobody writes into another
+// block) is race free.
+//
+// Two threads per pair of sites. Lane l < 32 of a wave and lane l + 32 share the even and
+// the odd site with one half index. In a hop the lower lane does the four forward hops of
+// the receiving site, the upper lane the four backward hops, both from the source
+// parity's spinors in LDS; afterwards v_permlane32_swap exchanges the halves of the two
+// partial sums, so that the lower lane holds spins 0-1 and the upper lane spins 2-3 of the
+// result. The clover term is diagonal in that chirality, as are all vector updates, so
+// between the hops every lane works on the 12 reals of its own chirality. Every wave is
+// busy in every phase and a thread's state is half a spinor per vector.
+// Both directions run one instruction stream: a backward hop is
+//   (1 + gamma) U^+ psi = conj((1 + gamma*) U^T conj(psi)),
+// the same product with the link transposed and conjugations that fold into the signs of
+// the projection's and the reconstruction's FMAs.
+//
+// What bounds it: with FP16 links and clover the issue of vector instructions (each hop is
+// 72 FMAs of SU(3) arithmetic per direction and lane, plus projection, reconstruction and
+// the transposition); with FP32 and FP64 fields also the links and clover that every MR
+// step re-reads through the caches (an 8x4^3 domain holds 295 KB of them in FP32, and 16 to
+// 32 domains share an XCD's 4 MB L2).
+// Two lanes per pair instead of one thread per pair or per site: the state of a lane is
+// half as large, so FP16 and FP32 run 4 waves per SIMD in 128 registers and FP64 2 waves in
+// 256 nearly without spills, no wave idles in one half of a hop, and the exchange costs 24
+// register instructions instead of an LDS round trip. Measured per half-sweep (4 MR steps)
+// against the one-thread-per-pair and one-thread-per-site kernels this replaced:
+//   4^4 lattice, 2^4 domains, FP64, 1 rhs        74.8 -> 28.0 us
+//   16^3 x 32, 8x4^3, FP32 / FP64, 1 rhs         68.8 -> 63.1 us / 442 -> 93.5 us
+//   24^3 x 48, 4^4, FP16, 5 rhs                   564 -> 445 us
+//   32^3 x 64, 8x4^3, FP16, 12 rhs               3860 -> 3250 us
+//   32^3 x 64, 8x4^3, FP32, 4 rhs                2187 -> 1487 us
+//
+// delta_o = A_o^-1 rho_o + kappa sum_i alpha_i A_o^-1 H_oe r_i is accumulated during the
+// MR steps from the vectors A_o^-1 H_oe r_i they form anyway: no closing hop and clover
+// product are needed.
 //
 // Clover input X per rhs: X = kappa T on even sites (A_e = 1 + X) and
 // X = A_o^-1 - 1 on odd sites (A_o^-1 = 1 + X).
-#include <cstdlib>
-#include <cstring>
-
 #include "blockgeo.hpp"
 #include "kernels.hpp"
 
@@ -45,659 +75,832 @@ template <class S, class SS, class P> struct SapArgs {  // S: links and clover, 
     int64_t psi_stride;  // elements per rhs
     const int *active;
     int nact;
-    int64_t nblk;  // blocks of one colour
     int colour, mode, write_state, nmr;
 };
 
-// Sum of v over a full wave of 64 lanes in a fixed order, the same on every lane: DPP
-// adds within each row of 16 lanes (lane ^ 1, lane ^ 2, then rotations by 4 and 8, after
-// which every lane holds its row's sum), then the four rows' sums read from lanes 0, 16,
-// 32 and 48. Register-to-register: no LDS round trip per step as with __shfl_xor.
-template <int CTRL> __device__ __forceinline__ float dpp_add(float v) {
-    return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF,
-                                                                     false));
+namespace {
+
+// ------------------------------------------------------------------ lanes
+// Other lane's register contents: the DPP control moves inside rows of 16 lanes.
+template <int CTRL> __device__ __forceinline__ float dpp_move(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
+}
+template <int CTRL> __device__ __forceinline__ double dpp_move(double v) {
+    int2 x = __builtin_bit_cast(int2, v);
+    x.x = __builtin_amdgcn_update_dpp(0, x.x, CTRL, 0xF, 0xF, false);
+    x.y = __builtin_amdgcn_update_dpp(0, x.y, CTRL, 0xF, 0xF, false);
+    return __builtin_bit_cast(double, x);
 }
 __device__ __forceinline__ float lane_value(float v, int lane) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
 }
-__device__ __forceinline__ float wave64_sum(float v) {
-    v = dpp_add<0xB1>(v);   // quad_perm [1,0,3,2]
-    v = dpp_add<0x4E>(v);   // quad_perm [2,3,0,1]
-    v = dpp_add<0x124>(v);  // row_ror:4
-    v = dpp_add<0x128>(v);  // row_ror:8
-    return ((lane_value(v, 0) + lane_value(v, 16)) + lane_value(v, 32)) + lane_value(v, 48);
+__device__ __forceinline__ double lane_value(double v, int lane) {
+    int2 x = __builtin_bit_cast(int2, v);
+    x.x = __builtin_amdgcn_readlane(x.x, lane);
+    x.y = __builtin_amdgcn_readlane(x.y, lane);
+    return __builtin_bit_cast(double, x);
 }
 
-// Sum three values over the workgroup in a fixed order; every thread gets the sums.
-template <class BK, class R>
-__device__ __forceinline__ void block_sum3(R &a, R &b, R &c, R *red) {
-    if constexpr (BK::W == 64 && sizeof(R) == 4) {
-        a = wave64_sum(a);
-        b = wave64_sum(b);
-        c = wave64_sum(c);
+// (a, b) -> a = { a of lanes 0-31, b of lanes 0-31 }, b = { a of lanes 32-63, b of lanes
+// 32-63 }: the upper half of a and the lower half of b change places.
+__device__ __forceinline__ void swap32(unsigned &a, unsigned &b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+__device__ __forceinline__ void swap32(float &a, float &b) {
+    unsigned x = __builtin_bit_cast(unsigned, a), y = __builtin_bit_cast(unsigned, b);
+    swap32(x, y);
+    a = __builtin_bit_cast(float, x);
+    b = __builtin_bit_cast(float, y);
+}
+__device__ __forceinline__ void swap32(double &a, double &b) {
+    uint2 x = __builtin_bit_cast(uint2, a), y = __builtin_bit_cast(uint2, b);
+    swap32(x.x, y.x);
+    swap32(x.y, y.y);
+    a = __builtin_bit_cast(double, x);
+    b = __builtin_bit_cast(double, y);
+}
+
+// Sum over the lanes of one block (GROUP = 64: the whole wave; GROUP = 8: lanes 8 g .. 8 g
+// + 7 and the same lanes + 32) in a fixed order, the same on each of them. Register to
+// register: DPP adds inside rows of 16 lanes, then the rows' sums.
+template <int GROUP, class R> __device__ __forceinline__ R lane_sum(R v) {
+    v = v + dpp_move<0xB1>(v);  // quad_perm [1,0,3,2]
+    v = v + dpp_move<0x4E>(v);  // quad_perm [2,3,0,1]
+    if constexpr (GROUP == 64) {
+        v = v + dpp_move<0x124>(v);  // row_ror:4
+        v = v + dpp_move<0x128>(v);  // row_ror:8
+        return ((lane_value(v, 0) + lane_value(v, 16)) + lane_value(v, 32)) + lane_value(v, 48);
     } else {
-#pragma unroll
-        for (int off = BK::W / 2; off > 0; off >>= 1) {
-            a += __shfl_xor(a, off, BK::W);
-            b += __shfl_xor(b, off, BK::W);
-            c += __shfl_xor(c, off, BK::W);
-        }
-    }
-    // the waves' sums of one value side by side (red is 16-byte aligned), so that every
-    // thread reads them with a few wide loads, all issued before the first add
-    constexpr int NW = BK::NW;
-    const int wv = threadIdx.x / 64;
-    if ((threadIdx.x & 63) == 0) {
-        red[wv] = a;
-        red[NW + wv] = b;
-        red[2 * NW + wv] = c;
-    }
-    __syncthreads();
-    R ra[NW], rb[NW], rc[NW];
-#pragma unroll
-    for (int q = 0; q < NW; ++q) {
-        ra[q] = red[q];
-        rb[q] = red[NW + q];
-        rc[q] = red[2 * NW + q];
-    }
-    a = ra[0];
-    b = rb[0];
-    c = rc[0];
-#pragma unroll
-    for (int q = 1; q < NW; ++q) {
-        a += ra[q];
-        b += rb[q];
-        c += rc[q];
+        v = v + dpp_move<0x141>(v);  // row_half_mirror: the other quad of 8 lanes
+        R w = v;
+        swap32(v, w);
+        return v + w;
     }
 }
 
-// Register policy: whether a thread keeps its links / clover in registers for the whole
-// block solve (re-reading them from the L1/L2 caches otherwise).
-#ifndef SAPDD_SAP_CACHE_LINKS
-#define SAPDD_SAP_CACHE_LINKS 0
-#endif
-#ifndef SAPDD_SAP_CACHE_CLOVER
-#define SAPDD_SAP_CACHE_CLOVER 0
-#endif
-
-#ifndef SAPDD_SAP_XLDS
-#define SAPDD_SAP_XLDS 1
-#endif
-
-// The clover of a thread's own site held in LDS (thread-private slots k * Vbh + s).
-template <class S, class R, int Vbh> struct LdsClover {
-    const S *x;
-    int s;
-    R sc;
-    __device__ __forceinline__ R at(int k) const {
-        if constexpr (Storage<S>::scaled) return (R)(float)x[k * Vbh + s];
-        else return (R)x[k * Vbh + s];
-    }
-    __device__ __forceinline__ R scale() const { return sc; }
+// ------------------------------------------------------------------ tile of one workgroup
+template <class BK, class R> struct Tile {
+    static constexpr int Vbh = BK::Vbh;
+    static constexpr int PER = Vbh < 32 ? 32 / Vbh : 1;  // (block, rhs) pairs per workgroup
+    static constexpr int NCOL = Vbh * PER;               // columns: even/odd site pairs
+    static constexpr int NT = 2 * NCOL;
+    static constexpr int NW = NT / 64;
+    static constexpr int CW = 16 / (int)sizeof(R);       // reals per 16-byte LDS vector
+    static constexpr int OWN = 12 / CW;                  // vectors of one chirality
+    static constexpr int BUF = 2 * OWN * NCOL;           // vectors per LDS buffer (one spinor per column)
+    typedef R VR __attribute__((ext_vector_type(16 / sizeof(R))));
 };
 
-#ifndef SAPDD_SAP_WAVES_PER_EU
-#define SAPDD_SAP_WAVES_PER_EU 2
-#endif
-
-// Hops into site x across its block faces in direction mu, from the neighbouring blocks'
-// corrections delta: rho += kappa * [ (1 - gamma) U_mu(x) delta(x + mu) on the forward
-// face, (1 + gamma) U_mu(x - mu)^+ delta(x - mu) on the backward face ].
-template <int MU, class BK, class S, class SS, class P, class R, class LK>
-__device__ __forceinline__ void gather_dir(const SapArgs<S, SS, P> &a, const SiteInfo &si, const LK &U,
-                                           const int (&g)[4], const SS *dlt, const float *dlt_sc, R kappa,
-                                           R (&rho)[24]) {
-    constexpr int Vbh = BK::Vbh;
-    const Geom &geo = a.geo;
-    const int B[4] = {BK::bx, BK::by, BK::bz, BK::bt};
-    if (!(si.fin & (1u << MU))) {  // x + mu lies in the next block
-        int gn[4] = {g[0], g[1], g[2], g[3]}, ln[4] = {si.l[0], si.l[1], si.l[2], si.l[3]};
-        R sg = 1;
-        if (++gn[MU] == geo.G[MU]) {
-            gn[MU] = 0;
-            if (MU == 3 && geo.antiperiodic) sg = -1;
+// A thread's place: column col (site half index s of its block), f = 0 lower lane (forward
+// hops, spins 0-1) or 1 upper lane (backward hops, spins 2-3); c = 1 or -1 accordingly.
+template <class BK, class R> struct Lane {
+    int s, f, col, col0;  // col0: first column of this thread's block
+    R c;
+    // For the site of either parity: the half index of its neighbour (forward or backward by
+    // f) in direction mu in byte mu of nb, s where that lies outside the block, and bit mu
+    // of in set where it lies inside.
+    unsigned nb[2], in[2];
+    __device__ __forceinline__ Lane() {
+        typedef Tile<BK, R> T;
+        const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+        f = lane >> 5;
+        col = 32 * wv + (lane & 31);
+        s = T::PER > 1 ? col % BK::Vbh : col;
+        col0 = T::PER > 1 ? col - s : 0;
+        c = f ? (R)-1 : (R)1;
+        const int B[4] = {BK::bx, BK::by, BK::bz, BK::bt};
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            int l[4];
+            local_coords(B, p, s, l);
+            in[p] = nb[p] = 0;
+#pragma unroll
+            for (int mu = 0; mu < 4; ++mu) {
+                int m[4] = {l[0], l[1], l[2], l[3]};
+                m[mu] += f ? -1 : 1;
+                const bool inside = f ? l[mu] > 0 : l[mu] < B[mu] - 1;
+                in[p] |= inside ? 1u << mu : 0u;
+                nb[p] |= (unsigned)(inside ? local_half_index(B, m) : s) << (8 * mu);
+            }
         }
-        ln[MU] = 0;
-        const int64_t nbp = 2 * block_index(geo.G, gn) + (1 - si.p);
-        const int ns = local_half_index(B, ln);
-        R d[24], h[12], u[18], uh[12];
-        load_site<R, 24>(dlt, dlt_sc, nbp, ns, Vbh, d);
-        project<MU, -1>(d, h);
-        U.template get<MU>(u);
-        su3_mul(u, h, uh);
-        accum_recon<MU, -1>(rho, uh, kappa * sg * U.scale());
     }
-    if (!(si.bin & (1u << MU))) {  // x - mu lies in the previous block
-        int gn[4] = {g[0], g[1], g[2], g[3]}, ln[4] = {si.l[0], si.l[1], si.l[2], si.l[3]};
-        R sg = 1;
-        if (--gn[MU] < 0) {
-            gn[MU] = geo.G[MU] - 1;
-            if (MU == 3 && geo.antiperiodic) sg = -1;
+    // Neighbour index and weight (1 inside, 0 outside) of direction MU at parity PR. The
+    // empty asm keeps what is computed from them out of the loop-invariant registers: as
+    // loop invariants the addresses of a hop's loads alone would fill the register file.
+    template <int PR, int MU> __device__ __forceinline__ int neighbour() const {
+        unsigned v = nb[PR];
+        asm volatile("" : "+v"(v));
+        return (int)(v >> (8 * MU) & 255u);
+    }
+    template <int PR, int MU> __device__ __forceinline__ R weight() const {
+        unsigned v = in[PR];
+        asm volatile("" : "+v"(v));
+        return (R)(int)(v >> MU & 1u);
+    }
+};
+
+// ------------------------------------------------------------------ loads
+// A block's part of a field: every load is a uniform base, a 32-bit offset per lane and a
+// constant. UNI (one block per workgroup): buffer loads, which take exactly that form and
+// return zeros past the block's end; else (2^4 blocks, several blocks per wave) plain
+// global loads from a base per lane.
+template <bool UNI> struct View;
+template <> struct View<true> {
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ void set(const void *p, int bytes) {
+        r = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00027000);
+    }
+};
+template <> struct View<false> {
+    const char *p;
+    __device__ __forceinline__ void set(const void *q, int) { p = (const char *)q; }
+};
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x3 __attribute__((ext_vector_type(3)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x3a __attribute__((ext_vector_type(3), aligned(4)));
+// N dwords (1..4) at byte offset off + C.
+template <int N> __device__ __forceinline__ void load_dwords(const View<true> &v, unsigned off, int C, unsigned *out) {
+    if constexpr (N == 1) {
+        out[0] = __builtin_amdgcn_raw_buffer_load_b32(v.r, (int)off, C, 0);
+    } else if constexpr (N == 2) {
+        const u32x2 x = __builtin_amdgcn_raw_buffer_load_b64(v.r, (int)off, C, 0);
+        out[0] = x[0], out[1] = x[1];
+    } else if constexpr (N == 3) {
+        const u32x3 x = __builtin_amdgcn_raw_buffer_load_b96(v.r, (int)off, C, 0);
+        out[0] = x[0], out[1] = x[1], out[2] = x[2];
+    } else {
+        const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(v.r, (int)off, C, 0);
+        out[0] = x[0], out[1] = x[1], out[2] = x[2], out[3] = x[3];
+    }
+}
+template <int N> __device__ __forceinline__ void load_dwords(const View<false> &v, unsigned off, int C, unsigned *out) {
+    const char *p = v.p + (size_t)off + C;
+    if constexpr (N == 1) {
+        out[0] = *gmem(reinterpret_cast<const unsigned *>(p));
+    } else if constexpr (N == 2) {
+        const u32x2 x = *gmem(reinterpret_cast<const u32x2 *>(p));
+        out[0] = x[0], out[1] = x[1];
+    } else if constexpr (N == 3) {
+        const u32x3a x = *(const SAPDD_GLOBAL u32x3a *)p;
+        out[0] = x[0], out[1] = x[1], out[2] = x[2];
+    } else {
+        const u32x4 x = *gmem(reinterpret_cast<const u32x4 *>(p));
+        out[0] = x[0], out[1] = x[1], out[2] = x[2], out[3] = x[3];
+    }
+}
+// Dwords D0 .. D0 + N - 1 of a site whose vectors of four dwords lie VS bytes apart, in
+// loads of exactly those bytes.
+template <int D0, int N, int VS, class VW>
+__device__ __forceinline__ void load_site_dwords(const VW &v, unsigned off, unsigned *out) {
+    if constexpr (N > 0) {
+        constexpr int here = 4 - D0 % 4 < N ? 4 - D0 % 4 : N;
+        load_dwords<here>(v, off, D0 / 4 * VS + D0 % 4 * 4, out);
+        load_site_dwords<D0 + here, N - here, VS>(v, off, out + here);
+    }
+}
+__device__ __forceinline__ float as_real(const unsigned *d, float) { return __builtin_bit_cast(float, d[0]); }
+__device__ __forceinline__ double as_real(const unsigned *d, double) {
+    return __builtin_bit_cast(double, (uint2){d[0], d[1]});
+}
+template <class VW> __device__ __forceinline__ float load_float(const VW &v, unsigned off) {
+    unsigned x;
+    load_dwords<1>(v, off, 0, &x);
+    return __builtin_bit_cast(float, x);
+}
+
+// ------------------------------------------------------------------ links
+// Link MU of the site whose vector 0 lies at byte offset off (vectors VS bytes apart),
+// transposed if tr: nine complex entries in storage precision. FP64 entries are vectors of
+// their own, so there the transposition is in the addresses; FP32 and FP16 entries change
+// places in registers (use: after their arrival).
+template <int MU, class S, int VS> struct Link;
+
+template <int MU, int VS> struct Link<MU, double, VS> {
+    unsigned d[36];
+    template <class VW> __device__ __forceinline__ void load(const VW &v, unsigned off, bool tr) {
+        const unsigned t = tr ? 2 * VS : 0, n = 2 * VS - t;
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {  // entry (a, b) or (b, a), 2 |a - b| vectors apart
+                const int lo = a < b ? 3 * a + b : 3 * b + a, dist = a < b ? b - a : a - b;
+                load_dwords<4>(v, off + (unsigned)dist * (a < b ? t : n), (9 * MU + lo) * VS, d + 4 * (3 * a + b));
+            }
+    }
+    __device__ __forceinline__ void arrive(bool) {}
+    template <class R> __device__ __forceinline__ R re(int k) const { return (R)as_real(d + 4 * k, 0.0); }
+    template <class R> __device__ __forceinline__ R im(int k) const { return (R)as_real(d + 4 * k + 2, 0.0); }
+};
+
+__device__ __forceinline__ void swap_if(bool tr, unsigned &a, unsigned &b) {
+    const unsigned x = tr ? b : a, y = tr ? a : b;
+    a = x;
+    b = y;
+}
+
+template <int MU, int VS> struct Link<MU, float, VS> {
+    unsigned d[18];
+    template <class VW> __device__ __forceinline__ void load(const VW &v, unsigned off, bool) {
+        load_site_dwords<18 * MU, 18, VS>(v, off, d);
+    }
+    __device__ __forceinline__ void arrive(bool tr) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            swap_if(tr, d[2 * 1 + q], d[2 * 3 + q]);
+            swap_if(tr, d[2 * 2 + q], d[2 * 6 + q]);
+            swap_if(tr, d[2 * 5 + q], d[2 * 7 + q]);
         }
-        ln[MU] = B[MU] - 1;
-        const int64_t nbp = 2 * block_index(geo.G, gn) + (1 - si.p);
-        const int ns = local_half_index(B, ln);
-        R d[24], h[12], u[18], uh[12];
-        load_site<R, 24>(dlt, dlt_sc, nbp, ns, Vbh, d);
-        load_reals<R, 72, 18 * MU, 18, S, true>(a.links, nullptr, nbp, ns, Vbh, u);
-        const R lsc = site_scale<R, S>(a.lscale, nbp, ns, Vbh);
-        project<MU, +1>(d, h);
-        su3_dag_mul(u, h, uh);
-        accum_recon<MU, +1>(rho, uh, kappa * sg * lsc);
+    }
+    template <class R> __device__ __forceinline__ R re(int k) const { return (R)as_real(d + 2 * k, 0.f); }
+    template <class R> __device__ __forceinline__ R im(int k) const { return (R)as_real(d + 2 * k + 1, 0.f); }
+};
+
+typedef half_t half2v __attribute__((ext_vector_type(2)));
+template <int MU, int VS> struct Link<MU, half_t, VS> {
+    unsigned d[9];  // without the site scale
+    template <class VW> __device__ __forceinline__ void load(const VW &v, unsigned off, bool) {
+        load_site_dwords<9 * MU, 9, VS>(v, off, d);
+    }
+    __device__ __forceinline__ void arrive(bool tr) {
+        swap_if(tr, d[1], d[3]);
+        swap_if(tr, d[2], d[6]);
+        swap_if(tr, d[5], d[7]);
+    }
+    template <class R> __device__ __forceinline__ R re(int k) const {
+        return (R)(float)__builtin_bit_cast(half2v, d[k])[0];
+    }
+    template <class R> __device__ __forceinline__ R im(int k) const {
+        return (R)(float)__builtin_bit_cast(half2v, d[k])[1];
+    }
+};
+
+// One hop in direction MU by this lane: acc += w (1 - gamma) U chi (forward, c = 1) or
+// w (1 + gamma) U^+ chi (backward, c = -1, u transposed). With sg = -c the projected half
+// spinor is h = up + sg G lo; backward it is conjugated, so its imaginary part is
+// c up - G lo in both cases (c sg = -1), and the result's imaginary part carries c.
+template <int MU, class R, class LK>
+__device__ __forceinline__ void hop_dir(const R (&chi)[24], const LK &u, R c, R w, R (&acc)[24]) {
+    R h[12], uh[12];
+    auto proj = [&](auto row) {
+        constexpr int ROW = decltype(row)::value;
+        constexpr int col = Grow<MU, ROW>::col, ph = Grow<MU, ROW>::ph;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            R re, im;
+            iph<ph>(chi[2 * (3 * (2 + col) + a)], chi[2 * (3 * (2 + col) + a) + 1], re, im);
+            h[2 * (3 * ROW + a)] = fmac(-c, re, chi[2 * (3 * ROW + a)]);
+            h[2 * (3 * ROW + a) + 1] = fmac(c, chi[2 * (3 * ROW + a) + 1], -im);
+        }
+    };
+    proj(std::integral_constant<int, 0>{});
+    proj(std::integral_constant<int, 1>{});
+#pragma unroll
+    for (int sp = 0; sp < 2; ++sp)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            R re = fmac(u.template re<R>(3 * a), h[6 * sp], (R)0);
+            R im = fmac(u.template re<R>(3 * a), h[6 * sp + 1], (R)0);
+            re = fmac(-u.template im<R>(3 * a), h[6 * sp + 1], re);
+            im = fmac(u.template im<R>(3 * a), h[6 * sp], im);
+#pragma unroll
+            for (int b = 1; b < 3; ++b) {
+                const R ur = u.template re<R>(3 * a + b), ui = u.template im<R>(3 * a + b);
+                re = fmac(ur, h[6 * sp + 2 * b], re);
+                re = fmac(-ui, h[6 * sp + 2 * b + 1], re);
+                im = fmac(ur, h[6 * sp + 2 * b + 1], im);
+                im = fmac(ui, h[6 * sp + 2 * b], im);
+            }
+            uh[6 * sp + 2 * a] = re;
+            uh[6 * sp + 2 * a + 1] = im;
+        }
+    // acc_up += w (re, c im); acc_lo += sg w i^ph (re, c im)
+    const R wc = w * c;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        acc[2 * k] = fmac(w, uh[2 * k], acc[2 * k]);
+        acc[2 * k + 1] = fmac(wc, uh[2 * k + 1], acc[2 * k + 1]);
+    }
+    auto recon = [&](auto row) {
+        constexpr int ROW = decltype(row)::value;
+        constexpr int col = GDrow<MU, ROW>::col, ph = GDrow<MU, ROW>::ph;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const R re = uh[2 * (3 * col + a)], im = uh[2 * (3 * col + a) + 1];
+            R &xr = acc[2 * (6 + 3 * ROW + a)], &xi = acc[2 * (6 + 3 * ROW + a) + 1];
+            // sg i^ph (re, c im) = (-c) i^ph (re, c im)
+            if constexpr (ph == 0) {
+                xr = fmac(-wc, re, xr);
+                xi = fmac(-w, im, xi);
+            } else if constexpr (ph == 1) {
+                xr = fmac(w, im, xr);
+                xi = fmac(-wc, re, xi);
+            } else if constexpr (ph == 2) {
+                xr = fmac(wc, re, xr);
+                xi = fmac(w, im, xi);
+            } else {
+                xr = fmac(-w, im, xr);
+                xi = fmac(wc, re, xi);
+            }
+        }
+    };
+    recon(std::integral_constant<int, 0>{});
+    recon(std::integral_constant<int, 1>{});
+}
+
+// The sum of the two lanes' partial spinors, each lane keeping its own chirality.
+template <class R> __device__ __forceinline__ void fold(R (&acc)[24], R (&out)[12]) {
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+        swap32(acc[k], acc[12 + k]);
+        out[k] = acc[k] + acc[12 + k];
     }
 }
 
-template <class BK, class S, class SS, class R, class P>
-__global__ __launch_bounds__(BK::NT) __attribute__((amdgpu_waves_per_eu(SAPDD_SAP_WAVES_PER_EU)))
-void sap_half_kernel(SapArgs<S, SS, P> a) {
-    constexpr int Vbh = BK::Vbh;
-    constexpr bool CACHE_L = sizeof(R) == 4 && SAPDD_SAP_CACHE_LINKS;
-    constexpr bool CACHE_X = sizeof(R) == 4 && SAPDD_SAP_CACHE_CLOVER;
-    // FP16 storage: even sites form A_e r during the odd sites' half of the MR step
-    // (4^4 blocks, 12 RHS: 425 -> 403 us per half-sweep). With FP32 or FP64 storage the
-    // extra live spinor across the hop costs more registers than the overlap gains
-    // (8x4^3 FP32: 84 -> 127 us), so A_e r is formed after the hop there.
-    constexpr bool EARLY_AE = Storage<S>::scaled;
-    // XL: on 8x4x4x4 blocks the even sites' clover is copied into LDS once and read from
-    // there in every MR step, and the hop uses one LDS buffer. With FP32 storage the links
-    // and clover of the 16 blocks an XCD works on at once exceed its 4 MB L2 otherwise
-    // (16^3x32, 1 RHS: 83.7 -> 74.6 us per half-sweep). Links in LDS, or the odd sites'
-    // clover as well (FP16), measured slower.
-    constexpr bool XL = SAPDD_SAP_XLDS && sizeof(R) == 4 && BK::Vbh == 256;
-    constexpr int HB = XL ? 1 : 2;
-    __shared__ R lds_hop[HopLds<BK, R, HB>::NBUF * HopLds<BK, R, HB>::PER];
-    __shared__ S xl[XL ? 72 * Vbh : 1];
-    __shared__ __align__(16) R red[3 * BK::NW];
-    HopLds<BK, R, HB> lds{lds_hop, 0};
-
-    const Geom &geo = a.geo;
-    const SiteInfo si = site_info<BK>(threadIdx.x);
-    // Workgroup w runs on XCD w mod 8. Number the (block, rhs) pairs so that the nact
-    // right-hand sides of one block follow each other on the same XCD: the block's links
-    // and clover are then re-read from that XCD's L2 instead of HBM.
-    const int64_t w = blockIdx.x;
-    const int64_t kq = w >> 3;
-    const int slot = (int)(kq % a.nact);
-    const int64_t kb = (kq / a.nact) * 8 + (w & 7);
-    if (kb >= a.nblk) return;  // padding of the last group of 8 (uniform per workgroup)
-    const int64_t b = colour_block(geo.G, a.colour, kb);
-    const int rhs = a.active[slot];
-    const int64_t bp = 2 * b + si.p;
-    const R kappa = (R)a.kappa[rhs];
-    const int64_t V = geo.V;
-    const bool even = si.p == 0;
-
-    SiteLinks<S, R, CACHE_L> U;
-    U.init(a.links, a.lscale, bp, si.s, Vbh);
-    SiteClover<S, R, CACHE_X> Xc;
-    Xc.init(a.X[rhs], a.Xsc ? a.Xsc[rhs] : nullptr, bp, si.s, Vbh);
-    LdsClover<S, R, Vbh> Xe{xl, si.s, (R)1};
-    if (XL && even) {
-        CloverRegs<S, R> c;
-        c.load(a.X[rhs], a.Xsc ? a.Xsc[rhs] : nullptr, bp, si.s, Vbh);
+// ------------------------------------------------------------------ own-chirality storage
+// The 12 reals of chirality f of site (bp, s) in a 24-real field, 16 bytes at a time (8 for
+// FP16, whose site has three 16-byte vectors).
+template <class R, class S>
+__device__ __forceinline__ void load_half(const S *data, const float *scale, int64_t bp, int s, int f, int Vbh,
+                                          R (&out)[12]) {
+    if constexpr (Storage<S>::scaled) {
+        typedef half_t h4 __attribute__((ext_vector_type(4)));
+        const R sc = (R)*gmem(scale + bp * Vbh + s);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const int q = 3 * f + i;
+            const h4 x = *gmem(reinterpret_cast<const h4 *>(data) + 2 * ((bp * 3 + (q >> 1)) * Vbh + s) + (q & 1));
+#pragma unroll
+            for (int w = 0; w < 4; ++w) out[4 * i + w] = (R)(float)x[w] * sc;
+        }
+    } else {
+        typedef typename Vec<S>::type VT;
         constexpr int W = Vec<S>::W;
 #pragma unroll
-        for (int v = 0; v < 72 / W; ++v)
+        for (int v = 0; v < 12 / W; ++v) {
+            const VT x = *gmem(reinterpret_cast<const VT *>(data) + (bp * (24 / W) + f * (12 / W) + v) * (int64_t)Vbh + s);
 #pragma unroll
-            for (int q = 0; q < W; ++q) xl[(v * W + q) * Vbh + si.s] = c.x[v][q];
-        Xe.sc = c.scale();
+            for (int w = 0; w < W; ++w) out[v * W + w] = (R)x[w];
+        }
     }
-    // even sites: T = (1 + X) in
-    auto mul_even = [&](const R(&in)[24], R(&out)[24]) {
-        if constexpr (XL) clover_mul(Xe, in, out, (R)1);
-        else Xc.mul(in, out, (R)1);
-    };
-
-    SS *dlt = a.delta + (int64_t)rhs * V * 24;
-    float *dlt_sc = a.delta_sc ? a.delta_sc + (int64_t)rhs * V : nullptr;
-
-    // Per-thread spinors. Even sites: A = MR residual r, B = MR solution; odd sites:
-    // A = block residual rho_o. T and H are scratch (H receives the in-block hops).
-    R A[24], B[24], T[24], H[24];
-
-    // ---- 1. block residual rho into A
-    if (a.mode < 2) {
-        double e[24];
-        load_site<double, 24>(a.eta + rhs * a.eta_stride, nullptr, bp, si.s, Vbh, e);
-        const double f = a.eta_scale ? a.eta_scale[(int64_t)rhs * a.eta_scale_stride] : 1.0;
+}
+// Store them; FP16 divides by the site's max |value| over both lanes and rounds to nearest
+// even (scale 0 stores zeros). Every lane of the wave calls this.
+template <class R, class S>
+__device__ __forceinline__ void store_half(S *data, float *scale, int64_t bp, int s, int f, int Vbh, const R (&in)[12]) {
+    if constexpr (Storage<S>::scaled) {
+        typedef half_t h4 __attribute__((ext_vector_type(4)));
+        float m = 0.f;
 #pragma unroll
-        for (int k = 0; k < 24; ++k) A[k] = (R)(e[k] * f);
-    } else if (even) {
-        load_site<R, 24>(a.rres + (int64_t)rhs * V * 12, a.rres_sc ? a.rres_sc + (int64_t)rhs * (V / 2) : nullptr, b,
-                         si.s, Vbh, A);
+        for (int k = 0; k < 12; ++k) m = fmaxf(m, fabsf((float)in[k]));
+        float o = m;
+        swap32(m, o);
+        m = fmaxf(m, o);
+        const float inv = fp16_site_inv(m);
+        if (f == 0) *gmem(scale + bp * Vbh + s) = inv > 0.f ? m : 0.f;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const int q = 3 * f + i;
+            h4 x;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) x[w] = (half_t)((float)in[4 * i + w] * inv);
+            *gmem(reinterpret_cast<h4 *>(data) + 2 * ((bp * 3 + (q >> 1)) * Vbh + s) + (q & 1)) = x;
+        }
     } else {
+        typedef typename Vec<S>::type VT;
+        constexpr int W = Vec<S>::W;
 #pragma unroll
-        for (int k = 0; k < 24; ++k) A[k] = 0;
-    }
-    if (a.mode >= 1) {
-        // rho(x) -= sum_y M_{x,y} delta(y) over hops from neighbouring blocks: M = -kappa * hop there.
-        int g[4];
-        block_coords(geo.G, b, g);
-        gather_dir<0, BK>(a, si, U, g, dlt, dlt_sc, kappa, A);
-        gather_dir<1, BK>(a, si, U, g, dlt, dlt_sc, kappa, A);
-        gather_dir<2, BK>(a, si, U, g, dlt, dlt_sc, kappa, A);
-        gather_dir<3, BK>(a, si, U, g, dlt, dlt_sc, kappa, A);
-    }
-
-    // ---- 2. bhat_e = rho_e + kappa H_eo A_o^-1 rho_o (odd: T = A_o^-1 rho_o)
-    if (!even) Xc.mul(A, T, (R)1);
-    block_hop<BK, true, true>(1, si, U, T, H, lds);
-    if (even) {
+        for (int v = 0; v < 12 / W; ++v) {
+            VT x;
 #pragma unroll
-        for (int k = 0; k < 24; ++k) {
-            A[k] = fmac(kappa, H[k], A[k]);
-            B[k] = 0;
+            for (int w = 0; w < W; ++w) x[w] = (S)in[v * W + w];
+            *gmem(reinterpret_cast<VT *>(data) + (bp * (24 / W) + f * (12 / W) + v) * (int64_t)Vbh + s) = x;
         }
-    }
-
-    // ---- 3. MR on Dhat = A_e - kappa^2 H_eo A_o^-1 H_oe
-    const R k2 = kappa * kappa;
-    for (int it = 0; it < a.nmr; ++it) {
-        block_hop<BK, true, true>(0, si, U, A, H, lds);  // odd: H = H_oe r
-        if (EARLY_AE && even) mul_even(A, T);  // even: T = A_e r (needs only r)
-        if (!even) Xc.mul(H, T, (R)1);           // odd: T = A_o^-1 H_oe r
-        // even: H = H_eo T; the reduction's barrier below separates these reads from the
-        // next hop's writes, so a single-buffer hop needs no barrier of its own at the end
-        block_hop<BK, false, true>(1, si, U, T, H, lds);
-        R pr_re = 0, pr_im = 0, pp = 0;
-        if (even) {
-            if (!EARLY_AE) mul_even(A, T);  // even: T = p = A_e r - kappa^2 H
-#pragma unroll
-            for (int k = 0; k < 24; ++k) T[k] = fmac(-k2, H[k], T[k]);
-#pragma unroll
-            for (int k = 0; k < 12; ++k) {
-                pr_re = fmac(T[2 * k], A[2 * k], pr_re);
-                pr_re = fmac(T[2 * k + 1], A[2 * k + 1], pr_re);
-                pr_im = fmac(T[2 * k], A[2 * k + 1], pr_im);
-                pr_im = fmac(-T[2 * k + 1], A[2 * k], pr_im);
-                pp = fmac(T[2 * k], T[2 * k], pp);
-                pp = fmac(T[2 * k + 1], T[2 * k + 1], pp);
-            }
-        }
-        block_sum3<BK>(pr_re, pr_im, pp, red);
-        R ar = 0, ai = 0;
-        if (pp > 0) {
-            const R inv = (R)1 / pp;  // one division for both parts
-            ar = pr_re * inv;
-            ai = pr_im * inv;
-        }
-        if (even) {
-#pragma unroll
-            for (int k = 0; k < 12; ++k) {
-                const R rr = A[2 * k], ri = A[2 * k + 1];
-                const R qr = T[2 * k], qi = T[2 * k + 1];
-                B[2 * k] = fmac(ar, rr, fmac(-ai, ri, B[2 * k]));
-                B[2 * k + 1] = fmac(ar, ri, fmac(ai, rr, B[2 * k + 1]));
-                A[2 * k] = fmac(-ar, qr, fmac(ai, qi, rr));
-                A[2 * k + 1] = fmac(-ar, qi, fmac(-ai, qr, ri));
-            }
-        }
-    }
-
-    // ---- 4. delta: even B, odd A_o^-1 (rho_o + kappa H_oe delta_e)
-    block_hop<BK, true, true>(0, si, U, B, H, lds);
-    if (!even) {
-#pragma unroll
-        for (int k = 0; k < 24; ++k) T[k] = fmac(kappa, H[k], A[k]);
-        Xc.mul(T, B, (R)1);  // odd: B = delta_o
-    }
-
-    // ---- 5. outputs: psi += delta, keep delta and the even-site residual
-    P *ps = a.psi + rhs * a.psi_stride;
-    if (a.mode == 2) {
-        R old[24];
-        load_site<R, 24>(ps, nullptr, bp, si.s, Vbh, old);
-#pragma unroll
-        for (int k = 0; k < 24; ++k) old[k] += B[k];
-        store_site<R, 24>(ps, nullptr, bp, si.s, Vbh, old);
-    } else {
-        store_site<R, 24>(ps, nullptr, bp, si.s, Vbh, B);
-    }
-    if (a.write_state) {
-        store_site<R, 24>(dlt, dlt_sc, bp, si.s, Vbh, B);
-        if (even)
-            store_site<R, 24>(a.rres + (int64_t)rhs * V * 12, a.rres_sc ? a.rres_sc + (int64_t)rhs * (V / 2) : nullptr,
-                              b, si.s, Vbh, A);
     }
 }
 
-// ---------------------------------------------------------------------------- pair form
-// The same half-sweep with one thread per pair of sites: thread s owns the even site and
-// the odd site with half index s of its block, so a workgroup has Vbh threads and every
-// wave works in both halves of a hop (it pushes from its site of the source parity, then
-// pulls into its site of the other parity). A workgroup then needs half the waves and
-// one hop buffer, and two (block, rhs) workgroups share a CU: while one waits at a
-// barrier or on memory, the other issues. The split-parity kernel above leaves the odd
-// waves idle while the even ones push and vice versa.
-//
-// The odd-site block residual rho_o, needed again at the end (delta_o = A_o^-1 (rho_o +
-// kappa H_oe delta_e)), is parked in the thread's own delta slots, which nobody reads
-// during this launch (the gather reads the other colour's corrections) and which the
-// thread overwrites with its final delta: 24 values of the arithmetic type fit the two
-// sites' slots in every storage precision, and no other thread touches them.
-template <class BK> struct PairBlk {
-    static constexpr int NT = BK::Vbh;
-    static constexpr int W = NT < 64 ? NT : 64;
-    static constexpr int NW = (NT + 63) / 64;
-};
-
-#ifndef SAPDD_SAP_LINK_AHEAD
-#define SAPDD_SAP_LINK_AHEAD 1
-#endif
-
-template <class LK> struct LinkStorage;
-template <class S, class R, bool C> struct LinkStorage<SiteLinks<S, R, C>> {
-    typedef S type;
-};
-
-// The 16-byte vectors that hold link MU of a thread's site, loaded ahead of their use: a
-// load issued after a barrier cannot be hoisted above it by the compiler, and the pull's
-// first link would otherwise wait out its full cache latency right after the barrier.
-template <int MU, class S> struct LinkAhead {
-    typedef typename Vec<S>::type VT;
-    static constexpr int W = Vec<S>::W, V0 = 18 * MU / W, V1 = (18 * MU + 17) / W, N = V1 - V0 + 1;
-    VT x[N];
-    template <class LK> __device__ __forceinline__ void load(const LK &U) {
-        const VT *p = reinterpret_cast<const VT *>(U.base);
+// The packed 6x6 block of one chirality: 36 reals in storage precision. FP16: nine 8-byte
+// pieces, piece q of a site in the (q & 1) half of vector q >> 1.
+template <class S, int VS> struct CloverHalf {
+    static constexpr int W = Vec<S>::W, DW = (int)sizeof(S) / 4;
+    unsigned d[36 * DW];
+    template <class VW> __device__ __forceinline__ void load(const VW &v, unsigned off, int f) {
+        const unsigned o = off + (f ? 36 / W * VS : 0);
 #pragma unroll
-        for (int v = 0; v < N; ++v) x[v] = ld_vec<false>(p + vec_index<S, 72>(U.bp, V0 + v, U.s, U.Vbh));
+        for (int q = 0; q < 36 / W; ++q) load_dwords<4>(v, o, q * VS, d + 4 * q);
     }
-    template <class R> __device__ __forceinline__ void get(R out[18]) const {
+    template <class R> __device__ __forceinline__ R at(int k) const { return (R)as_real(d + DW * k, (S)0); }
+};
+template <int VS> struct CloverHalf<half_t, VS> {
+    unsigned d[18];
+    template <class VW> __device__ __forceinline__ void load(const VW &v, unsigned off, int f) {
+        // piece 9 f + i: for f = 1 an even i starts in the upper half of vector 4 + i / 2,
+        // an odd i in the lower half of vector 5 + i / 2
+        const unsigned oe = off + (f ? 4 * VS + 8 : 0), oo = off + (f ? 5 * VS : 8);
 #pragma unroll
-        for (int k = 0; k < 18; ++k) {
-            const int q = 18 * MU + k - V0 * W;
-            if constexpr (Storage<S>::scaled) out[k] = (R)(float)x[q / W][q % W];
-            else out[k] = (R)x[q / W][q % W];
+        for (int i = 0; i < 9; ++i) load_dwords<2>(v, i & 1 ? oo : oe, i / 2 * VS, d + 2 * i);
+    }
+    template <class R> __device__ __forceinline__ R at(int k) const {
+        return (R)(float)__builtin_bit_cast(half2v, d[k / 2])[k % 2];
+    }
+};
+
+// out = in + fx X in for one chirality (fx: the FP16 site scale, else 1).
+template <class XR, class R>
+__device__ __forceinline__ void clover_half_mul(const XR &X, const R (&in)[12], R (&out)[12], R fx) {
+    R t[12];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        const R d = X.template at<R>(i);
+        t[2 * i] = fmac(d, in[2 * i], (R)0);
+        t[2 * i + 1] = fmac(d, in[2 * i + 1], (R)0);
+    }
+#pragma unroll
+    for (int i = 0; i < 6; ++i)
+#pragma unroll
+        for (int j = i + 1; j < 6; ++j) {
+            const int q = 6 + 2 * (i * 5 - i * (i - 1) / 2 + (j - i - 1));
+            const R xr = X.template at<R>(q), xi = X.template at<R>(q + 1);
+            t[2 * i] = fmac(xr, in[2 * j], t[2 * i]);
+            t[2 * i] = fmac(-xi, in[2 * j + 1], t[2 * i]);
+            t[2 * i + 1] = fmac(xr, in[2 * j + 1], t[2 * i + 1]);
+            t[2 * i + 1] = fmac(xi, in[2 * j], t[2 * i + 1]);
+            t[2 * j] = fmac(xr, in[2 * i], t[2 * j]);
+            t[2 * j] = fmac(xi, in[2 * i + 1], t[2 * j]);
+            t[2 * j + 1] = fmac(xr, in[2 * i + 1], t[2 * j + 1]);
+            t[2 * j + 1] = fmac(-xi, in[2 * i], t[2 * j + 1]);
         }
+#pragma unroll
+    for (int k = 0; k < 12; ++k) out[k] = fmac(fx, t[k], in[k]);
+}
+
+// ------------------------------------------------------------------ one block
+// The resident fields of a thread's block.
+template <class BK, class S, class R> struct BlockView {
+    static constexpr bool UNI = Tile<BK, R>::PER == 1;
+    static constexpr int VS = BK::Vbh * 16;           // bytes between a site's vectors
+    static constexpr int NV = 72 / Vec<S>::W;         // vectors per link / clover site
+    View<UNI> links, X, lsc, xsc;
+    __device__ __forceinline__ static unsigned off(int p, int s) { return (unsigned)(p * NV * VS + s * 16); }
+    __device__ __forceinline__ R lscale(int p, int s) const {
+        if constexpr (Storage<S>::scaled) return (R)load_float(lsc, (unsigned)((p * BK::Vbh + s) * 4));
+        else return (R)1;
+    }
+    __device__ __forceinline__ R xscale(int p, int s) const {
+        if constexpr (Storage<S>::scaled) return (R)load_float(xsc, (unsigned)((p * BK::Vbh + s) * 4));
+        else return (R)1;
+    }
+    // out = (1 + X) in at the site of parity P
+    template <int P> __device__ __forceinline__ void clover(const Lane<BK, R> &ln, const R (&in)[12], R (&out)[12]) const {
+        CloverHalf<S, VS> c;
+        int s = ln.s;
+        asm volatile("" : "+v"(s));
+        c.load(X, off(P, s), ln.f);
+        clover_half_mul(c, in, out, xscale(P, s));
     }
 };
 
-// pull_dir (branch-free) with the link of direction MU given.
-template <int MU, class BK, class R, class LK, class LA>
-__device__ __forceinline__ void pull_dir_ahead(const SiteInfo &si, const LK &U, const LA &la, R (&out)[24],
-                                               const R *__restrict__ sp, const R *__restrict__ hb) {
-    constexpr int Vbh = BK::Vbh;
-    const bool f = (si.fin >> MU) & 1u, b = (si.bin >> MU) & 1u;
-    {
-        R chi[24], h[12], uh[12], u[18];
-        const int n = si.nbf[MU];
-#pragma unroll
-        for (int k = 0; k < 24; ++k) chi[k] = sp[k * Vbh + n];
-        project<MU, -1>(chi, h);
-        la.get(u);
-        su3_mul(u, h, uh);
-        accum_recon<MU, -1>(out, uh, f ? U.scale() : (R)0);
+// One direction of an in-block hop into the sites of parity PR: the link and its weight
+// (0 for a lane without the neighbour inside the block), loaded ahead of their use. The
+// link sits at the receiving site (forward) or at the source (backward).
+template <int PR, int MU, class BK, class S, class R> struct HopLink {
+    Link<MU, S, BlockView<BK, S, R>::VS> u;
+    R sc;
+    __device__ __forceinline__ void load(const BlockView<BK, S, R> &bv, const Lane<BK, R> &ln) {
+        const int n = ln.template neighbour<PR, MU>();
+        const int lp = ln.f ? 1 - PR : PR, ls = ln.f ? n : ln.s;
+        u.load(bv.links, bv.off(lp, ls), ln.f != 0);
+        sc = bv.lscale(lp, ls);
     }
-    {
-        R uh[12];
-        const int n = si.nbb[MU];
+};
+template <int PR, int MU, class BK, class S, class R>
+__device__ __forceinline__ void hop_mu(HopLink<PR, MU, BK, S, R> &l, const Lane<BK, R> &ln,
+                                       const typename Tile<BK, R>::VR *buf, R (&acc)[24]) {
+    typedef Tile<BK, R> T;
+    const int at = ln.col0 + ln.template neighbour<PR, MU>();
+    R chi[24];
 #pragma unroll
-        for (int k = 0; k < 12; ++k) uh[k] = hb[(MU * 12 + k) * Vbh + n];
-        accum_recon<MU, +1>(out, uh, b ? (R)1 : (R)0);
+    for (int q = 0; q < 2 * T::OWN; ++q) {
+        const typename T::VR x = buf[q * T::NCOL + at];
+#pragma unroll
+        for (int k = 0; k < T::CW; ++k) chi[q * T::CW + k] = x[k];
+    }
+    l.u.arrive(ln.f != 0);
+    hop_dir<MU>(chi, l.u, ln.c, ln.template weight<PR, MU>() * l.sc, acc);
+}
+
+// The in-block hops into the sites of parity PR from the spinors of the other parity in
+// buf: out = own chirality of sum_mu [ (1 - gamma) U(x) chi(x + mu) + (1 + gamma) U^+(x - mu) chi(x - mu) ].
+// Lanes without the neighbour take their own column's slot with weight zero: the face
+// conditions differ between the lanes of a wave, so a branch would save no issue slot.
+// l0: the link of direction 0, loaded by the caller. The scheduling barriers keep one
+// direction's spinor and two links in registers at a time.
+template <int PR, class BK, class S, class R>
+__device__ __forceinline__ void block_hop_half(HopLink<PR, 0, BK, S, R> &l0, const BlockView<BK, S, R> &bv,
+                                               const Lane<BK, R> &ln, const typename Tile<BK, R>::VR *buf,
+                                               R (&out)[12]) {
+    R acc[24];
+#pragma unroll
+    for (int k = 0; k < 24; ++k) acc[k] = 0;
+    HopLink<PR, 1, BK, S, R> l1;
+    l1.load(bv, ln);
+    hop_mu(l0, ln, buf, acc);
+    __builtin_amdgcn_sched_barrier(0);
+    HopLink<PR, 2, BK, S, R> l2;
+    l2.load(bv, ln);
+    hop_mu(l1, ln, buf, acc);
+    __builtin_amdgcn_sched_barrier(0);
+    HopLink<PR, 3, BK, S, R> l3;
+    l3.load(bv, ln);
+    hop_mu(l2, ln, buf, acc);
+    __builtin_amdgcn_sched_barrier(0);
+    hop_mu(l3, ln, buf, acc);
+    fold(acc, out);
+}
+
+template <class BK, class R>
+__device__ __forceinline__ void put(typename Tile<BK, R>::VR *buf, const Lane<BK, R> &ln, const R (&v)[12]) {
+    typedef Tile<BK, R> T;
+#pragma unroll
+    for (int q = 0; q < T::OWN; ++q) {
+        typename T::VR x;
+#pragma unroll
+        for (int k = 0; k < T::CW; ++k) x[k] = v[q * T::CW + k];
+        buf[(ln.f * T::OWN + q) * T::NCOL + ln.col] = x;
+    }
+}
+template <class BK, class R>
+__device__ __forceinline__ void get_own(const typename Tile<BK, R>::VR *buf, const Lane<BK, R> &ln, R (&v)[12]) {
+    typedef Tile<BK, R> T;
+#pragma unroll
+    for (int q = 0; q < T::OWN; ++q) {
+        const typename T::VR x = buf[(ln.f * T::OWN + q) * T::NCOL + ln.col];
+#pragma unroll
+        for (int k = 0; k < T::CW; ++k) v[q * T::CW + k] = x[k];
     }
 }
 
-// In-block hop between the parities in pair form: this thread pushes `in` from its site
-// of parity SRC and receives `out` at its site of the other parity. Both SAP kernels take
-// the branch-free directions: they are bound by instruction issue, not by memory.
-template <int SRC, class BK, bool TAIL = true, class R, class LK, int WANT>
-__device__ __forceinline__ void pair_hop(const SiteInfo &se, const SiteInfo &so, const LK &Ue, const LK &Uo,
-                                         const R (&in)[24], R (&out)[24], HopLds<BK, R, WANT> &lds) {
+// Hops into the site of parity PR across its block's faces, from the neighbouring blocks'
+// corrections delta: rho += kappa * (forward face hop by the lower lane, backward by the
+// upper lane).
+template <int PR, class BK, class S, class SS, class R, class P>
+__device__ __forceinline__ void gather_half(const SapArgs<S, SS, P> &a, const Lane<BK, R> &ln, const int (&g)[4],
+                                            int64_t b, const SS *dlt, const float *dlt_sc, R kappa, R (&rho)[12]) {
     constexpr int Vbh = BK::Vbh;
-    R *__restrict__ sp = lds.sp();
-    R *__restrict__ hb = lds.hb();
-    const SiteInfo &ss = SRC == 0 ? se : so;
-    const SiteInfo &sr = SRC == 0 ? so : se;
-    const LK &Us = SRC == 0 ? Ue : Uo;
-    const LK &Ur = SRC == 0 ? Uo : Ue;
-#if SAPDD_SAP_LINK_AHEAD
-    LinkAhead<0, typename LinkStorage<LK>::type> la;
-    la.load(Ur);
-#endif
+    constexpr int VS = Vbh * 16, NV = 72 / Vec<S>::W;
+    const Geom &geo = a.geo;
+    const int B[4] = {BK::bx, BK::by, BK::bz, BK::bt};
+    int l[4];
+    local_coords(B, PR, ln.s, l);
+    R acc[24], sum[12];
 #pragma unroll
-    for (int k = 0; k < 24; ++k) sp[k * Vbh + ss.s] = in[k];
-    push_dir<0, BK, true>(ss, Us, in, hb);
-    push_dir<1, BK, true>(ss, Us, in, hb);
-    push_dir<2, BK, true>(ss, Us, in, hb);
-    push_dir<3, BK, true>(ss, Us, in, hb);
-    __syncthreads();
+    for (int k = 0; k < 24; ++k) acc[k] = 0;
+    static_for<0, 4>([&](auto m) {
+        constexpr int MU = decltype(m)::value;
+        if (!(ln.in[PR] >> MU & 1u)) {
+            int gn[4] = {g[0], g[1], g[2], g[3]}, lm[4] = {l[0], l[1], l[2], l[3]};
+            R sg = 1;
+            gn[MU] += ln.f ? -1 : 1;
+            if (gn[MU] == geo.G[MU] || gn[MU] < 0) {
+                gn[MU] = ln.f ? geo.G[MU] - 1 : 0;
+                if (MU == 3 && geo.antiperiodic) sg = -1;
+            }
+            lm[MU] = ln.f ? B[MU] - 1 : 0;
+            const int64_t nbp = 2 * block_index(geo.G, gn) + (1 - PR);
+            const int ns = local_half_index(B, lm);
+            const int64_t lbp = ln.f ? nbp : 2 * b + PR;
+            const int ls = ln.f ? ns : ln.s;
+            View<false> lv;
+            lv.set(reinterpret_cast<const char *>(a.links) + lbp * (NV * VS), 0);
+            Link<MU, S, VS> u;
+            u.load(lv, (unsigned)(ls * 16), ln.f != 0);
+            u.arrive(ln.f != 0);
+            R chi[24];
+            load_site<R, 24>(dlt, dlt_sc, nbp, ns, Vbh, chi);
+            hop_dir<MU>(chi, u, ln.c, kappa * sg * site_scale<R, S>(a.lscale, lbp, ls, Vbh), acc);
+        }
+    });
+    fold(acc, sum);
 #pragma unroll
-    for (int k = 0; k < 24; ++k) out[k] = 0;
-#if SAPDD_SAP_LINK_AHEAD
-    pull_dir_ahead<0, BK>(sr, Ur, la, out, sp, hb);
-#else
-    pull_dir<0, BK, true>(sr, Ur, out, sp, hb);
-#endif
-    pull_dir<1, BK, true>(sr, Ur, out, sp, hb);
-    pull_dir<2, BK, true>(sr, Ur, out, sp, hb);
-    pull_dir<3, BK, true>(sr, Ur, out, sp, hb);
-    if constexpr (HopLds<BK, R, WANT>::NBUF == 2) {
-        lds.cur ^= 1;
-    } else if constexpr (TAIL) {
+    for (int k = 0; k < 12; ++k) rho[k] += sum[k];
+}
+
+// Sum three values over the threads of one block in a fixed order; every thread gets the
+// sums. red: 3 * NW reals, 16-byte aligned.
+template <class BK, class R> __device__ __forceinline__ void block_sum3(R &a, R &b, R &c, R *red) {
+    typedef Tile<BK, R> T;
+    constexpr int GROUP = T::PER > 1 ? BK::Vbh : 64;
+    a = lane_sum<GROUP>(a);
+    b = lane_sum<GROUP>(b);
+    c = lane_sum<GROUP>(c);
+    if constexpr (T::NW > 1) {
+        constexpr int NW = T::NW;
+        const int wv = threadIdx.x >> 6;
+        if ((threadIdx.x & 63) == 0) {
+            red[wv] = a;
+            red[NW + wv] = b;
+            red[2 * NW + wv] = c;
+        }
+        __syncthreads();
+        R ra[NW], rb[NW], rc[NW];  // wide loads, all issued before the first add
+#pragma unroll
+        for (int q = 0; q < NW; ++q) {
+            ra[q] = red[q];
+            rb[q] = red[NW + q];
+            rc[q] = red[2 * NW + q];
+        }
+        a = ra[0];
+        b = rb[0];
+        c = rc[0];
+#pragma unroll
+        for (int q = 1; q < NW; ++q) {
+            a += ra[q];
+            b += rb[q];
+            c += rc[q];
+        }
+    } else {
         __syncthreads();
     }
 }
 
-// Park / fetch 24 values of type R in the 16-byte vectors of the thread's two delta slots
-// (even site first), in a thread-private order.
-template <class S, class R>
-__device__ __forceinline__ void park(S *dlt, int64_t b, int s, int Vbh, const R (&v)[24]) {
-    typedef typename Vec<S>::type VS;
-    typedef R VR __attribute__((ext_vector_type(16 / sizeof(R))));
-    constexpr int PER = 16 / sizeof(R);
-    constexpr int NV = 24 / PER;           // vectors to park
-    constexpr int NS = 24 / Vec<S>::W;     // vectors per site slot
-    static_assert(NV <= 2 * NS, "two delta slots hold the parked spinor");
-    VS *p = reinterpret_cast<VS *>(dlt);
-#pragma unroll
-    for (int q = 0; q < NV; ++q) {
-        VR x;
-#pragma unroll
-        for (int w = 0; w < PER; ++w) x[w] = v[q * PER + w];
-        const int site_p = q / NS, vv = q % NS;
-        *gmem(reinterpret_cast<VR *>(p + vec_index<S, 24>(2 * b + site_p, vv, s, Vbh))) = x;
-    }
-}
-template <class S, class R>
-__device__ __forceinline__ void fetch(const S *dlt, int64_t b, int s, int Vbh, R (&v)[24]) {
-    typedef typename Vec<S>::type VS;
-    typedef R VR __attribute__((ext_vector_type(16 / sizeof(R))));
-    constexpr int PER = 16 / sizeof(R);
-    constexpr int NV = 24 / PER;
-    constexpr int NS = 24 / Vec<S>::W;
-    const VS *p = reinterpret_cast<const VS *>(dlt);
-#pragma unroll
-    for (int q = 0; q < NV; ++q) {
-        const int site_p = q / NS, vv = q % NS;
-        const VR x = *gmem(reinterpret_cast<const VR *>(p + vec_index<S, 24>(2 * b + site_p, vv, s, Vbh)));
-#pragma unroll
-        for (int w = 0; w < PER; ++w) v[q * PER + w] = x[w];
-    }
+#ifndef SAPDD_SAP_WPE32
+#define SAPDD_SAP_WPE32 4
+#endif
+#ifndef SAPDD_SAP_WPE16
+#define SAPDD_SAP_WPE16 4
+#endif
+template <class BK, class S, class R> constexpr int sap_waves_per_eu() {
+    if (BK::Vbh < 32) return sizeof(R) == 8 ? 1 : 2;
+    return sizeof(R) == 8 ? 2 : sizeof(S) == 4 ? SAPDD_SAP_WPE32 : SAPDD_SAP_WPE16;
 }
 
-#ifndef SAPDD_SAP_PAIR_WAVES_PER_EU
-#define SAPDD_SAP_PAIR_WAVES_PER_EU 2
-#endif
+}  // namespace
 
 template <class BK, class S, class SS, class R, class P>
-__global__ __launch_bounds__(PairBlk<BK>::NT) __attribute__((amdgpu_waves_per_eu(SAPDD_SAP_PAIR_WAVES_PER_EU)))
-void sap_pair_kernel(SapArgs<S, SS, P> a) {
+__global__ __launch_bounds__((Tile<BK, R>::NT)) __attribute__((amdgpu_waves_per_eu(sap_waves_per_eu<BK, S, R>())))
+void sap_kernel(SapArgs<S, SS, P> a) {
     constexpr int Vbh = BK::Vbh;
-    typedef PairBlk<BK> PB;
-    // one hop buffer: two workgroups per CU need their LDS to fit twice
-    __shared__ R lds_hop[HopLds<BK, R, 1>::PER];
-    __shared__ __align__(16) R red[3 * PB::NW];
-    HopLds<BK, R, 1> lds{lds_hop, 0};
+    typedef Tile<BK, R> T;
+    typedef typename T::VR VR;
+    __shared__ VR lds[2 * T::BUF];
+    __shared__ __align__(16) R red[3 * T::NW];
+    VR *buf0 = lds, *buf1 = lds + T::BUF;  // even-site vectors r, odd-site vectors
 
     const Geom &geo = a.geo;
-    const int s = threadIdx.x;
-    const SiteInfo se = site_info<BK>(s);
-    const SiteInfo so = site_info<BK>(Vbh + s);
-    // (block, rhs) numbering as in the split-parity kernel: the rhs of one block follow
-    // each other on one XCD, so its links and clover come from that XCD's L2
-    const int64_t w = blockIdx.x;
-    const int64_t kq = w >> 3;
-    const int slot = (int)(kq % a.nact);
-    const int64_t kb = (kq / a.nact) * 8 + (w & 7);
-    if (kb >= a.nblk) return;  // padding of the last group of 8 (uniform per workgroup)
+    const Lane<BK, R> ln;
+    int slot;
+    int64_t kb;
+    // The block grid is even in every direction, so the count of blocks of one colour is a
+    // multiple of 8 and no workgroup is partly filled.
+    if constexpr (T::PER > 1) {  // several (block, rhs) pairs per wave
+        const int64_t q = (int64_t)blockIdx.x * T::PER + ln.col / Vbh;
+        slot = (int)(q % a.nact);
+        kb = q / a.nact;
+    } else {
+        // Workgroup w runs on XCD w mod 8. Number the (block, rhs) pairs so that the nact
+        // right-hand sides of one block follow each other on the same XCD: the block's
+        // links and clover are then re-read from that XCD's L2 instead of HBM.
+        const int64_t w = blockIdx.x;
+        const int64_t kq = w >> 3;
+        slot = (int)(kq % a.nact);
+        kb = (kq / a.nact) * 8 + (w & 7);
+    }
     const int64_t b = colour_block(geo.G, a.colour, kb);
     const int rhs = a.active[slot];
     const R kappa = (R)a.kappa[rhs];
     const int64_t V = geo.V;
 
-    SiteLinks<S, R, false> Ue, Uo;
-    Ue.init(a.links, a.lscale, 2 * b, s, Vbh);
-    Uo.init(a.links, a.lscale, 2 * b + 1, s, Vbh);
-    SiteClover<S, R, false> Xe, Xo;  // X = kappa T (even: A_e = 1 + X), A_o^-1 - 1 (odd)
-    const S *Xr = (const S *)a.X[rhs];
-    const float *Xs = a.Xsc ? a.Xsc[rhs] : nullptr;
-    Xe.init(Xr, Xs, 2 * b, s, Vbh);
-    Xo.init(Xr, Xs, 2 * b + 1, s, Vbh);
+    BlockView<BK, S, R> bv;
+    constexpr int BB = 2 * Vbh * 72 * (int)sizeof(S);  // bytes of links or clover per block
+    bv.links.set(a.links + 2 * b * 72 * Vbh, BB);
+    bv.X.set(a.X[rhs] + 2 * b * 72 * Vbh, BB);
+    if constexpr (Storage<S>::scaled) {
+        bv.lsc.set(a.lscale + 2 * b * Vbh, 2 * Vbh * 4);
+        bv.xsc.set(a.Xsc[rhs] + 2 * b * Vbh, 2 * Vbh * 4);
+    }
 
     SS *dlt = a.delta + (int64_t)rhs * V * 24;
     float *dlt_sc = a.delta_sc ? a.delta_sc + (int64_t)rhs * V : nullptr;
     SS *rr = a.rres + (int64_t)rhs * V * 12;
     float *rr_sc = a.rres_sc ? a.rres_sc + (int64_t)rhs * (V / 2) : nullptr;
 
-    // A: even rho, then the MR residual r; B: odd rho, then the MR solution x (even);
-    // T, H: scratch
-    R A[24], B[24], T[24], H[24];
+    // own chirality of: A = even rho, then the MR residual r; B = MR solution x; O = odd
+    // rho, then delta_o; H, Q scratch
+    R A[12], B[12], O[12], H[12], Q[12];
 
-    // ---- 1. block residual rho (even into A, odd into B)
+    // ---- 1. block residual rho (even into A, odd into O)
     if (a.mode < 2) {
         const double *eta = a.eta + rhs * a.eta_stride;
         const double f = a.eta_scale ? a.eta_scale[(int64_t)rhs * a.eta_scale_stride] : 1.0;
-        double e[24];
-        load_site<double, 24>(eta, nullptr, 2 * b, s, Vbh, e);
+        double e[12];
+        load_half<double, double>(eta, nullptr, 2 * b, ln.s, ln.f, Vbh, e);
 #pragma unroll
-        for (int k = 0; k < 24; ++k) A[k] = (R)(e[k] * f);
-        load_site<double, 24>(eta, nullptr, 2 * b + 1, s, Vbh, e);
+        for (int k = 0; k < 12; ++k) A[k] = (R)(e[k] * f);
+        load_half<double, double>(eta, nullptr, 2 * b + 1, ln.s, ln.f, Vbh, e);
 #pragma unroll
-        for (int k = 0; k < 24; ++k) B[k] = (R)(e[k] * f);
+        for (int k = 0; k < 12; ++k) O[k] = (R)(e[k] * f);
     } else {
-        load_site<R, 24>(rr, rr_sc, b, s, Vbh, A);
+        load_half<R, SS>(rr, rr_sc, b, ln.s, ln.f, Vbh, A);
 #pragma unroll
-        for (int k = 0; k < 24; ++k) B[k] = 0;
+        for (int k = 0; k < 12; ++k) O[k] = 0;
     }
     if (a.mode >= 1) {
         int g[4];
         block_coords(geo.G, b, g);
-        gather_dir<0, BK>(a, se, Ue, g, dlt, dlt_sc, kappa, A);
-        gather_dir<1, BK>(a, se, Ue, g, dlt, dlt_sc, kappa, A);
-        gather_dir<2, BK>(a, se, Ue, g, dlt, dlt_sc, kappa, A);
-        gather_dir<3, BK>(a, se, Ue, g, dlt, dlt_sc, kappa, A);
-        gather_dir<0, BK>(a, so, Uo, g, dlt, dlt_sc, kappa, B);
-        gather_dir<1, BK>(a, so, Uo, g, dlt, dlt_sc, kappa, B);
-        gather_dir<2, BK>(a, so, Uo, g, dlt, dlt_sc, kappa, B);
-        gather_dir<3, BK>(a, so, Uo, g, dlt, dlt_sc, kappa, B);
+        gather_half<1, BK, S, SS, R>(a, ln, g, b, dlt, dlt_sc, kappa, O);
+        gather_half<0, BK, S, SS, R>(a, ln, g, b, dlt, dlt_sc, kappa, A);
     }
-    // rho_o is needed again at the end: park it in this thread's delta slots
-    park<SS, R>(dlt, b, s, Vbh, B);
 
-    // ---- 2. bhat_e = rho_e + kappa H_eo A_o^-1 rho_o
-    Xo.mul(B, T, (R)1);
-    pair_hop<1, BK>(se, so, Ue, Uo, T, H, lds);
+    // ---- 2. O = A_o^-1 rho_o, bhat_e = rho_e + kappa H_eo A_o^-1 rho_o
+    bv.template clover<1>(ln, O, Q);
 #pragma unroll
-    for (int k = 0; k < 24; ++k) {
+    for (int k = 0; k < 12; ++k) O[k] = Q[k];
+    HopLink<0, 0, BK, S, R> le;
+    HopLink<1, 0, BK, S, R> lo;
+    le.load(bv, ln);
+    put<BK, R>(buf1, ln, O);
+    __syncthreads();
+    block_hop_half<0>(le, bv, ln, buf1, H);
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
         A[k] = fmac(kappa, H[k], A[k]);
         B[k] = 0;
     }
 
     // ---- 3. MR on Dhat = A_e - kappa^2 H_eo A_o^-1 H_oe
+    // Three barriers a step: r in buf0, A_o^-1 H_oe r in buf1, the inner products. A buffer
+    // is written again only after a later barrier than its last reads.
     const R k2 = kappa * kappa;
     for (int it = 0; it < a.nmr; ++it) {
-        // odd: H = H_oe r, then T = A_o^-1 H. The hop's closing barrier comes after the
-        // clover product (which touches no LDS), so a wave done with its pull goes on
-        // to it instead of waiting, and its clover loads are not held behind a barrier.
-        pair_hop<0, BK, false>(se, so, Ue, Uo, A, H, lds);
-        Xo.mul(H, T, (R)1);
+        lo.load(bv, ln);
+        put<BK, R>(buf0, ln, A);
         __syncthreads();
-        // even: H = H_eo T; the reduction's barrier below separates these reads from the
-        // next hop's writes
-        pair_hop<1, BK, false>(se, so, Ue, Uo, T, H, lds);
-        Xe.mul(A, T, (R)1);  // even: T = A_e r, then p = T - kappa^2 H
+        block_hop_half<1>(lo, bv, ln, buf0, H);  // odd: H_oe r
+        bv.template clover<1>(ln, H, Q);         // odd: Q = A_o^-1 H_oe r
+        le.load(bv, ln);
+        put<BK, R>(buf1, ln, Q);
+        __syncthreads();
+        block_hop_half<0>(le, bv, ln, buf1, H);  // even: H_eo Q
+        bv.template clover<0>(ln, A, Q);         // even: A_e r, then p = A_e r - kappa^2 H
         R pr_re = 0, pr_im = 0, pp = 0;
 #pragma unroll
-        for (int k = 0; k < 24; ++k) T[k] = fmac(-k2, H[k], T[k]);
+        for (int k = 0; k < 12; ++k) Q[k] = fmac(-k2, H[k], Q[k]);
 #pragma unroll
-        for (int k = 0; k < 12; ++k) {
-            pr_re = fmac(T[2 * k], A[2 * k], pr_re);
-            pr_re = fmac(T[2 * k + 1], A[2 * k + 1], pr_re);
-            pr_im = fmac(T[2 * k], A[2 * k + 1], pr_im);
-            pr_im = fmac(-T[2 * k + 1], A[2 * k], pr_im);
-            pp = fmac(T[2 * k], T[2 * k], pp);
-            pp = fmac(T[2 * k + 1], T[2 * k + 1], pp);
+        for (int k = 0; k < 6; ++k) {
+            pr_re = fmac(Q[2 * k], A[2 * k], pr_re);
+            pr_re = fmac(Q[2 * k + 1], A[2 * k + 1], pr_re);
+            pr_im = fmac(Q[2 * k], A[2 * k + 1], pr_im);
+            pr_im = fmac(-Q[2 * k + 1], A[2 * k], pr_im);
+            pp = fmac(Q[2 * k], Q[2 * k], pp);
+            pp = fmac(Q[2 * k + 1], Q[2 * k + 1], pp);
         }
-        block_sum3<PB>(pr_re, pr_im, pp, red);
+        block_sum3<BK, R>(pr_re, pr_im, pp, red);
         R ar = 0, ai = 0;
         if (pp > 0) {
             const R inv = (R)1 / pp;  // one division for both parts
             ar = pr_re * inv;
             ai = pr_im * inv;
         }
+        get_own<BK, R>(buf1, ln, H);  // this step's A_o^-1 H_oe r
+        const R kr = kappa * ar, ki = kappa * ai;
 #pragma unroll
-        for (int k = 0; k < 12; ++k) {
+        for (int k = 0; k < 6; ++k) {
             const R rr_ = A[2 * k], ri = A[2 * k + 1];
-            const R qr = T[2 * k], qi = T[2 * k + 1];
+            const R qr = Q[2 * k], qi = Q[2 * k + 1];
+            const R tr = H[2 * k], ti = H[2 * k + 1];
             B[2 * k] = fmac(ar, rr_, fmac(-ai, ri, B[2 * k]));
             B[2 * k + 1] = fmac(ar, ri, fmac(ai, rr_, B[2 * k + 1]));
+            O[2 * k] = fmac(kr, tr, fmac(-ki, ti, O[2 * k]));
+            O[2 * k + 1] = fmac(kr, ti, fmac(ki, tr, O[2 * k + 1]));
             A[2 * k] = fmac(-ar, qr, fmac(ai, qi, rr_));
             A[2 * k + 1] = fmac(-ar, qi, fmac(-ai, qr, ri));
         }
     }
 
-    // ---- 4. delta: even B, odd A_o^-1 (rho_o + kappa H_oe delta_e)
-    pair_hop<0, BK, false>(se, so, Ue, Uo, B, H, lds);  // the last use of LDS: no closing barrier
-    fetch<SS, R>(dlt, b, s, Vbh, T);
-#pragma unroll
-    for (int k = 0; k < 24; ++k) T[k] = fmac(kappa, H[k], T[k]);
-    Xo.mul(T, H, (R)1);  // H = delta_o
-
-    // ---- 5. outputs: psi += delta, keep delta and the even-site residual
+    // ---- 4. outputs: psi += delta (even B, odd O), keep delta and the even-site residual
     P *ps = a.psi + rhs * a.psi_stride;
+    R old[12];
     if (a.mode == 2) {
-        R old[24];
-        load_site<R, 24>(ps, nullptr, 2 * b, s, Vbh, old);
+        load_half<R, P>(ps, nullptr, 2 * b, ln.s, ln.f, Vbh, H);
+        load_half<R, P>(ps, nullptr, 2 * b + 1, ln.s, ln.f, Vbh, old);
 #pragma unroll
-        for (int k = 0; k < 24; ++k) old[k] += B[k];
-        store_site<R, 24>(ps, nullptr, 2 * b, s, Vbh, old);
-        load_site<R, 24>(ps, nullptr, 2 * b + 1, s, Vbh, old);
-#pragma unroll
-        for (int k = 0; k < 24; ++k) old[k] += H[k];
-        store_site<R, 24>(ps, nullptr, 2 * b + 1, s, Vbh, old);
+        for (int k = 0; k < 12; ++k) {
+            H[k] += B[k];
+            old[k] += O[k];
+        }
+        store_half<R, P>(ps, nullptr, 2 * b, ln.s, ln.f, Vbh, H);
+        store_half<R, P>(ps, nullptr, 2 * b + 1, ln.s, ln.f, Vbh, old);
     } else {
-        store_site<R, 24>(ps, nullptr, 2 * b, s, Vbh, B);
-        store_site<R, 24>(ps, nullptr, 2 * b + 1, s, Vbh, H);
+        store_half<R, P>(ps, nullptr, 2 * b, ln.s, ln.f, Vbh, B);
+        store_half<R, P>(ps, nullptr, 2 * b + 1, ln.s, ln.f, Vbh, O);
     }
     if (a.write_state) {
-        store_site<R, 24>(dlt, dlt_sc, 2 * b, s, Vbh, B);
-        store_site<R, 24>(dlt, dlt_sc, 2 * b + 1, s, Vbh, H);
-        store_site<R, 24>(rr, rr_sc, b, s, Vbh, A);
+        store_half<R, SS>(dlt, dlt_sc, 2 * b, ln.s, ln.f, Vbh, B);
+        store_half<R, SS>(dlt, dlt_sc, 2 * b + 1, ln.s, ln.f, Vbh, O);
+        store_half<R, SS>(rr, rr_sc, b, ln.s, ln.f, Vbh, A);
     }
-}
-
-// Which form runs a half-sweep (both compute the same half-sweep, each in its own fixed
-// order; both are checked against the oracle). The pair form needs two workgroups per CU to pay off, and its FP32-storage variants
-// spill registers: measured on 48^3 x 96 (FP16 storage, 12 RHS, 124416 workgroups) it
-// takes 23.5 ms per half-sweep against 29.3 ms, on 16^3 x 32 (FP32 storage, one RHS, 128
-// workgroups) 142 us against 73 us. So: the pair form for FP16 links and clover on
-// lattices with at least one block of each colour per CU, the split-parity form otherwise
-// (it also serves FP64 and 2^4 blocks). The choice depends on the geometry only, never on
-// how many right-hand sides share the launch, so a right-hand side gets the same bits
-// alone and in any batch. SAPDD_SAP_KERNEL=pair or =split in the environment forces one.
-static int sap_form_override() {
-    static const int v = [] {
-        const char *e = getenv("SAPDD_SAP_KERNEL");
-        if (e && strcmp(e, "split") == 0) return 1;
-        if (e && strcmp(e, "pair") == 0) return 2;
-        return 0;
-    }();
-    return v;
-}
-template <class S> static bool sap_pair_form(int64_t nblk) {
-    const int o = sap_form_override();
-    if (o) return o == 2;
-    return Storage<S>::scaled && nblk >= 256;
 }
 
 template <class BK, class S, class SS, class R, class P>
@@ -721,21 +924,14 @@ static hipError_t sap_typed(const Geom &geo, const SapArgsHost &h, int colour, i
     a.psi_stride = (int64_t)h.psi_stride_rhs * geo.V * 24;
     a.active = h.active;
     a.nact = h.nact;
-    a.nblk = geo.Nd / 2;
     a.colour = colour;
     a.mode = mode;
     a.write_state = ws;
     a.nmr = h.nmr;
-    const int64_t nwg = (geo.Nd / 2 + 7) / 8 * 8 * h.nact;
-    if (nwg > 0x7fffffff) return hipErrorInvalidValue;
-    dim3 grid((unsigned)nwg);
-    if constexpr (sizeof(R) == 4 && BK::Vbh >= 128) {
-        if (sap_pair_form<S>(a.nblk)) {
-            hipLaunchKernelGGL((sap_pair_kernel<BK, S, SS, R, P>), grid, dim3(PairBlk<BK>::NT), 0, st, a);
-            return hipGetLastError();
-        }
-    }
-    hipLaunchKernelGGL((sap_half_kernel<BK, S, SS, R, P>), grid, dim3(BK::NT), 0, st, a);
+    typedef Tile<BK, R> T;
+    const int64_t nblk = geo.Nd / 2, nwg = nblk * h.nact / T::PER;
+    if (nblk % 8 != 0 || nwg > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((sap_kernel<BK, S, SS, R, P>), dim3((unsigned)nwg), dim3(T::NT), 0, st, a);
     return hipGetLastError();
 }
 

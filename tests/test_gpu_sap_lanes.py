@@ -1,0 +1,48 @@
+"""The Schwarz half-sweep kernel where its lane layout can go wrong, against the NumPy oracle.
+
+A wave holds 32 pairs of sites: on 2^4 domains four (domain, right-hand side) pairs share
+one wave, so with three right-hand sides of different kappa the lanes of a wave carry
+different clover fields and kappas; on 4^4 and 8x4^3 domains a workgroup is four or eight
+waves whose inner products meet in LDS. The number of MR steps reaches from one (the
+accumulated odd-site correction is its first term only) to five. Tolerances are those of
+the element-wise parity tests: about ten times the rounding of the storage precision.
+"""
+import numpy as np
+import pytest
+
+import synthetic
+from oracle import sap as osap
+from oracle import wilson
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"f64": 1e-10, "f32": 1e-6, "f16": 1e-3, "f16l": 1e-3}
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_1502_04025_amd import Context
+    c = Context(0)
+    yield c
+    c.close()
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16", "f16l"])
+@pytest.mark.parametrize("dims,block,nmr", [((8, 4, 4, 12), (2, 2, 2, 2), 1), ((8, 8, 8, 8), (4, 4, 4, 4), 5),
+                                            ((16, 8, 8, 8), (8, 4, 4, 4), 1)])
+def test_three_kappas_share_the_waves(ctx, dims, block, nmr, prec):
+    kap = [0.125, 0.118, 0.121]
+    u = synthetic.gauge_field(dims, 0.3, 81)
+    eta = synthetic.gaussian_source(dims, len(kap), 82)
+    t = wilson.clover_term(u, 1.0)
+    f = ctx.load_gauge(u, block)
+    f.compute_clover(1.0)
+    out = f.sap(np.array(kap), eta, nmr=nmr, ncy=2, prec=prec)
+    f.free()
+    for r, k in enumerate(kap):
+        ref = osap.sap(osap.BlockSystem(u, t, k, block), eta[r], 2, nmr)
+        d = out[r] - ref
+        assert np.linalg.norm(d) <= TOL[prec] * np.linalg.norm(ref), (r, prec)
+        assert np.abs(d).max() <= 4 * TOL[prec] * np.abs(ref).max(), (r, prec)
