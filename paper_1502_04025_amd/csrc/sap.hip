@@ -40,10 +40,12 @@
 // register instructions instead of an LDS round trip. Measured per half-sweep (4 MR steps)
 // against the one-thread-per-pair and one-thread-per-site kernels this replaced:
 //   4^4 lattice, 2^4 domains, FP64, 1 rhs        74.8 -> 28.0 us
-//   16^3 x 32, 8x4^3, FP32 / FP64, 1 rhs         68.8 -> 63.1 us / 442 -> 93.5 us
-//   24^3 x 48, 4^4, FP16, 5 rhs                   564 -> 445 us
-//   32^3 x 64, 8x4^3, FP16, 12 rhs               3860 -> 3250 us
-//   32^3 x 64, 8x4^3, FP32, 4 rhs                2187 -> 1487 us
+//   16^3 x 32, 8x4^3, FP32 / FP64, 1 rhs         68.8 -> 42.3 us / 442 -> 85.5 us
+//   24^3 x 48, 4^4, FP16, 5 rhs                   564 -> 430 us
+//   32^3 x 64, 8x4^3, FP16, 12 rhs               3860 -> 3153 us
+//   32^3 x 64, 8x4^3, FP32, 4 rhs                2187 -> 1262 us
+// At 32^3 x 64, 12 rhs the FP16 kernel issues 7970 vector instructions per wave and is
+// issuing them 88% of the time.
 //
 // delta_o = A_o^-1 rho_o + kappa sum_i alpha_i A_o^-1 H_oe r_i is accumulated during the
 // MR steps from the vectors A_o^-1 H_oe r_i they form anyway: no closing hop and clover
@@ -337,22 +339,35 @@ template <int MU, int VS> struct Link<MU, half_t, VS> {
     }
 };
 
-// One hop in direction MU by this lane: acc += w (1 - gamma) U chi (forward, c = 1) or
-// w (1 + gamma) U^+ chi (backward, c = -1, u transposed). With sg = -c the projected half
-// spinor is h = up + sg G lo; backward it is conjugated, so its imaginary part is
-// c up - G lo in both cases (c sg = -1), and the result's imaginary part carries c.
-template <int MU, class R, class LK>
-__device__ __forceinline__ void hop_dir(const R (&chi)[24], const LK &u, R c, R w, R (&acc)[24]) {
-    R h[12], uh[12];
+// A neighbour's spinor as it is read: component k as an R. FP16 sites keep their halves
+// (without the site scale), which the projection's FMAs take as they are.
+template <class R, class S> struct Chi {
+    R v[24];
+    __device__ __forceinline__ R operator()(int k) const { return v[k]; }
+};
+template <class R> struct Chi<R, half_t> {
+    unsigned d[12];
+    __device__ __forceinline__ R operator()(int k) const {
+        return (R)(float)__builtin_bit_cast(half2v, d[k / 2])[k % 2];
+    }
+};
+
+// One hop in direction MU by this lane, up to the reconstruction: (1 - gamma) U chi
+// (forward, c = 1) or (1 + gamma) U^+ chi (backward, c = -1, u transposed). With sg = -c
+// the projected half spinor is h = up + sg G lo; backward it is conjugated, so its
+// imaginary part is c up - G lo in both cases (c sg = -1), and that of uh carries c.
+template <int MU, class R, class CHI, class LK>
+__device__ __forceinline__ void hop_half(const CHI &chi, const LK &u, R c, R (&uh)[12]) {
+    R h[12];
     auto proj = [&](auto row) {
         constexpr int ROW = decltype(row)::value;
         constexpr int col = Grow<MU, ROW>::col, ph = Grow<MU, ROW>::ph;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             R re, im;
-            iph<ph>(chi[2 * (3 * (2 + col) + a)], chi[2 * (3 * (2 + col) + a) + 1], re, im);
-            h[2 * (3 * ROW + a)] = fmac(-c, re, chi[2 * (3 * ROW + a)]);
-            h[2 * (3 * ROW + a) + 1] = fmac(c, chi[2 * (3 * ROW + a) + 1], -im);
+            iph<ph>(chi(2 * (3 * (2 + col) + a)), chi(2 * (3 * (2 + col) + a) + 1), re, im);
+            h[2 * (3 * ROW + a)] = fmac(-c, re, chi(2 * (3 * ROW + a)));
+            h[2 * (3 * ROW + a) + 1] = fmac(c, chi(2 * (3 * ROW + a) + 1), -im);
         }
     };
     proj(std::integral_constant<int, 0>{});
@@ -376,8 +391,9 @@ __device__ __forceinline__ void hop_dir(const R (&chi)[24], const LK &u, R c, R 
             uh[6 * sp + 2 * a] = re;
             uh[6 * sp + 2 * a + 1] = im;
         }
-    // acc_up += w (re, c im); acc_lo += sg w i^ph (re, c im)
-    const R wc = w * c;
+}
+// The reconstruction: acc_up += w (re, c im), acc_lo += sg w i^ph (re, c im), wc = w c.
+template <int MU, class R> __device__ __forceinline__ void hop_recon(const R (&uh)[12], R w, R wc, R (&acc)[24]) {
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
         acc[2 * k] = fmac(w, uh[2 * k], acc[2 * k]);
@@ -408,6 +424,12 @@ __device__ __forceinline__ void hop_dir(const R (&chi)[24], const LK &u, R c, R 
     };
     recon(std::integral_constant<int, 0>{});
     recon(std::integral_constant<int, 1>{});
+}
+template <int MU, class R, class CHI, class LK>
+__device__ __forceinline__ void hop_dir(const CHI &chi, const LK &u, R c, R w, R (&acc)[24]) {
+    R uh[12];
+    hop_half<MU>(chi, u, c, uh);
+    hop_recon<MU>(uh, w, w * c, acc);
 }
 
 // The sum of the two lanes' partial spinors, each lane keeping its own chirality.
@@ -580,12 +602,12 @@ __device__ __forceinline__ void hop_mu(HopLink<PR, MU, BK, S, R> &l, const Lane<
                                        const typename Tile<BK, R>::VR *buf, R (&acc)[24]) {
     typedef Tile<BK, R> T;
     const int at = ln.col0 + ln.template neighbour<PR, MU>();
-    R chi[24];
+    Chi<R, R> chi;
 #pragma unroll
     for (int q = 0; q < 2 * T::OWN; ++q) {
         const typename T::VR x = buf[q * T::NCOL + at];
 #pragma unroll
-        for (int k = 0; k < T::CW; ++k) chi[q * T::CW + k] = x[k];
+        for (int k = 0; k < T::CW; ++k) chi.v[q * T::CW + k] = x[k];
     }
     l.u.arrive(ln.f != 0);
     hop_dir<MU>(chi, l.u, ln.c, ln.template weight<PR, MU>() * l.sc, acc);
@@ -596,8 +618,9 @@ __device__ __forceinline__ void hop_mu(HopLink<PR, MU, BK, S, R> &l, const Lane<
 // Lanes without the neighbour take their own column's slot with weight zero: the face
 // conditions differ between the lanes of a wave, so a branch would save no issue slot.
 // l0: the link of direction 0, loaded by the caller. The scheduling barriers keep one
-// direction's spinor and two links in registers at a time.
-template <int PR, class BK, class S, class R>
+// direction's spinor in registers at a time, and one link or, with AHEAD, two: the next
+// direction's is then on its way while this one's is used.
+template <int PR, bool AHEAD, class BK, class S, class R>
 __device__ __forceinline__ void block_hop_half(HopLink<PR, 0, BK, S, R> &l0, const BlockView<BK, S, R> &bv,
                                                const Lane<BK, R> &ln, const typename Tile<BK, R>::VR *buf,
                                                R (&out)[12]) {
@@ -605,17 +628,20 @@ __device__ __forceinline__ void block_hop_half(HopLink<PR, 0, BK, S, R> &l0, con
 #pragma unroll
     for (int k = 0; k < 24; ++k) acc[k] = 0;
     HopLink<PR, 1, BK, S, R> l1;
-    l1.load(bv, ln);
+    HopLink<PR, 2, BK, S, R> l2;
+    HopLink<PR, 3, BK, S, R> l3;
+    if constexpr (AHEAD) l1.load(bv, ln);
     hop_mu(l0, ln, buf, acc);
     __builtin_amdgcn_sched_barrier(0);
-    HopLink<PR, 2, BK, S, R> l2;
-    l2.load(bv, ln);
+    if constexpr (!AHEAD) l1.load(bv, ln);
+    if constexpr (AHEAD) l2.load(bv, ln);
     hop_mu(l1, ln, buf, acc);
     __builtin_amdgcn_sched_barrier(0);
-    HopLink<PR, 3, BK, S, R> l3;
-    l3.load(bv, ln);
+    if constexpr (!AHEAD) l2.load(bv, ln);
+    if constexpr (AHEAD) l3.load(bv, ln);
     hop_mu(l2, ln, buf, acc);
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (!AHEAD) l3.load(bv, ln);
     hop_mu(l3, ln, buf, acc);
     fold(acc, out);
 }
@@ -642,15 +668,128 @@ __device__ __forceinline__ void get_own(const typename Tile<BK, R>::VR *buf, con
     }
 }
 
-// Hops into the site of parity PR across its block's faces, from the neighbouring blocks'
-// corrections delta: rho += kappa * (forward face hop by the lower lane, backward by the
-// upper lane).
-template <int PR, class BK, class S, class SS, class R, class P>
-__device__ __forceinline__ void gather_half(const SapArgs<S, SS, P> &a, const Lane<BK, R> &ln, const int (&g)[4],
-                                            int64_t b, const SS *dlt, const float *dlt_sc, R kappa, R (&rho)[12]) {
+// ------------------------------------------------------------------ gather
+// The spinor of site (bp, s) for the face hops, without its FP16 scale.
+template <class R, class SS>
+__device__ __forceinline__ void load_chi(const SS *data, int64_t bp, int s, int Vbh, Chi<R, SS> &chi) {
+    if constexpr (Storage<SS>::scaled) {
+#pragma unroll
+        for (int v = 0; v < 3; ++v) {
+            const u32x4 x = *gmem(reinterpret_cast<const u32x4 *>(data) + (bp * 3 + v) * (int64_t)Vbh + s);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) chi.d[4 * v + k] = x[k];
+        }
+    } else {
+        load_site<R, 24>(data, nullptr, bp, s, Vbh, chi.v);
+    }
+}
+// The block beyond this lane's face in direction MU (forward for f = 0) and the sign of
+// the hop into it.
+template <int MU> __device__ __forceinline__ int64_t face_block(const Geom &geo, const int (&g)[4], int f, int &sg) {
+    int gn[4] = {g[0], g[1], g[2], g[3]};
+    sg = 1;
+    gn[MU] += f ? -1 : 1;
+    if (gn[MU] == geo.G[MU] || gn[MU] < 0) {
+        gn[MU] = f ? geo.G[MU] - 1 : 0;
+        if (MU == 3 && geo.antiperiodic) sg = -1;
+    }
+    return block_index(geo.G, gn);
+}
+// One hop across a face in direction MU into site sr of parity PR, from site sn of block
+// nb, up to the reconstruction: uh with its weight w (kappa, the sign, the FP16 scales).
+template <int PR, int MU, class BK, class S, class SS, class R, class P>
+__device__ __forceinline__ R face_hop(const SapArgs<S, SS, P> &a, int64_t b, int64_t nb, int sr, int sn, int f, R c,
+                                      R ksg, const SS *dlt, const float *dlt_sc, R (&uh)[12]) {
     constexpr int Vbh = BK::Vbh;
     constexpr int VS = Vbh * 16, NV = 72 / Vec<S>::W;
-    const Geom &geo = a.geo;
+    const int64_t nbp = 2 * nb + (1 - PR);
+    const int64_t lbp = f ? nbp : 2 * b + PR;  // the link sits at the receiver (forward) or the source
+    const int ls = f ? sn : sr;
+    View<false> lv;
+    lv.set(reinterpret_cast<const char *>(a.links) + lbp * (NV * VS), 0);
+    Link<MU, S, VS> u;
+    u.load(lv, (unsigned)(ls * 16), f != 0);
+    Chi<R, SS> chi;
+    load_chi<R, SS>(dlt, nbp, sn, Vbh, chi);
+    const R w = ksg * site_scale<R, S>(a.lscale, lbp, ls, Vbh) * site_scale<R, SS>(dlt_sc, nbp, sn, Vbh);
+    u.arrive(f != 0);
+    hop_half<MU>(chi, u, c, uh);
+    return w;
+}
+
+// The face hops of one block and parity, shared out over the workgroup: a block has
+// Vbh / B_mu receiving sites per face, 224 over the four directions on 8x4^3 and 128 on
+// 4^4 blocks, at most one for every lane of either half (forward faces the lower lanes,
+// backward the upper). Each direction takes whole waves, so a wave runs one direction's
+// code for 32 sites a half; hopping where the sites sit instead would run all four
+// directions in every wave with a quarter (an eighth in x) of its lanes (32^3 x 64, FP16,
+// 12 rhs: 9070 against 7970 instructions per wave, 3270 against 3153 us on 8x4^3 and 3159
+// against 3015 us on 4^4 blocks).
+template <class BK> struct Faces {
+    static constexpr int ext(int mu) { return BK::ext(mu); }
+    static constexpr int count(int mu) { return BK::Vbh / BK::ext(mu); }
+    static constexpr int first(int mu) { return mu == 0 ? 0 : first(mu - 1) + count(mu - 1); }
+    static constexpr int total = first(3) + count(3);
+    // the two directions other than t = MU that number the face's sites beside x (y for MU = 0)
+    static constexpr int o1(int mu) { return mu == 0 ? 2 : mu == 1 ? 2 : 1; }
+    static constexpr int o2(int mu) { return mu == 3 ? 2 : 3; }
+    static_assert(BK::Vbh < 32 || (count(0) % 32 == 0 && count(1) % 32 == 0 && count(2) % 32 == 0 && count(3) % 32 == 0 &&
+                                   total <= BK::Vbh), "whole waves per direction");
+    // coordinates of receiving site j of parity p on the face l[MU] = at
+    template <int MU> static __device__ __forceinline__ void site(int j, int p, int at, int (&l)[4]) {
+        constexpr int h = MU == 0 ? BK::by / 2 : BK::bx / 2, e1 = BK::ext(o1(MU));
+        const int k = j % h, r = j / h;
+        l[MU] = at;
+        l[o1(MU)] = r % e1;
+        l[o2(MU)] = r / e1;
+        constexpr int in = MU == 0 ? 1 : 0;  // the direction that the parity fixes to k
+        const int q = (p + at + r % e1 + r / e1) & 1;
+        l[in] = 2 * k + q;
+    }
+    template <int MU> static __device__ __forceinline__ int number(const int (&l)[4]) {
+        constexpr int h = MU == 0 ? BK::by / 2 : BK::bx / 2, e1 = BK::ext(o1(MU));
+        return (l[MU == 0 ? 1 : 0] >> 1) + h * (l[o1(MU)] + e1 * l[o2(MU)]);
+    }
+};
+
+// This wave's face hops into the sites of parity PR: w uh of face site q (by first + j) and
+// half f into vector column f * total + q of buf.
+template <int PR, class BK, class S, class SS, class R, class P>
+__device__ __forceinline__ void face_items(const SapArgs<S, SS, P> &a, const Lane<BK, R> &ln, const int (&g)[4], int64_t b,
+                                           const SS *dlt, const float *dlt_sc, R kappa,
+                                           typename Tile<BK, R>::VR *buf) {
+    typedef Tile<BK, R> T;
+    typedef Faces<BK> F;
+    const int B[4] = {BK::bx, BK::by, BK::bz, BK::bt};
+    const int q0 = 32 * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    static_for<0, 4>([&](auto m) {
+        constexpr int MU = decltype(m)::value;
+        if (q0 >= F::first(MU) && q0 < F::first(MU) + F::count(MU)) {  // uniform
+            const int q = q0 + (threadIdx.x & 31);
+            int lr[4], lb[4], sgf, sgb;
+            F::template site<MU>(q - F::first(MU), PR, ln.f ? 0 : B[MU] - 1, lr);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) lb[d] = lr[d];
+            lb[MU] = ln.f ? B[MU] - 1 : 0;
+            const int64_t bf = face_block<MU>(a.geo, g, 0, sgf), bb = face_block<MU>(a.geo, g, 1, sgb);
+            R uh[12];
+            const R w = face_hop<PR, MU, BK>(a, b, ln.f ? bb : bf, local_half_index(B, lr), local_half_index(B, lb), ln.f,
+                                             ln.c, kappa * (R)(ln.f ? sgb : sgf), dlt, dlt_sc, uh);
+#pragma unroll
+            for (int v = 0; v < T::OWN; ++v) {
+                typename T::VR x;
+#pragma unroll
+                for (int k = 0; k < T::CW; ++k) x[k] = w * uh[v * T::CW + k];
+                buf[v * (2 * F::total) + ln.f * F::total + q] = x;
+            }
+        }
+    });
+}
+// rho += the face hops into this thread's site of parity PR, from buf.
+template <int PR, class BK, class R>
+__device__ __forceinline__ void face_sum(const Lane<BK, R> &ln, const typename Tile<BK, R>::VR *buf, R (&rho)[12]) {
+    typedef Tile<BK, R> T;
+    typedef Faces<BK> F;
     const int B[4] = {BK::bx, BK::by, BK::bz, BK::bt};
     int l[4];
     local_coords(B, PR, ln.s, l);
@@ -660,26 +799,42 @@ __device__ __forceinline__ void gather_half(const SapArgs<S, SS, P> &a, const La
     static_for<0, 4>([&](auto m) {
         constexpr int MU = decltype(m)::value;
         if (!(ln.in[PR] >> MU & 1u)) {
-            int gn[4] = {g[0], g[1], g[2], g[3]}, lm[4] = {l[0], l[1], l[2], l[3]};
-            R sg = 1;
-            gn[MU] += ln.f ? -1 : 1;
-            if (gn[MU] == geo.G[MU] || gn[MU] < 0) {
-                gn[MU] = ln.f ? geo.G[MU] - 1 : 0;
-                if (MU == 3 && geo.antiperiodic) sg = -1;
+            const int q = F::first(MU) + F::template number<MU>(l);
+            R uh[12];
+#pragma unroll
+            for (int v = 0; v < T::OWN; ++v) {
+                const typename T::VR x = buf[v * (2 * F::total) + ln.f * F::total + q];
+#pragma unroll
+                for (int k = 0; k < T::CW; ++k) uh[v * T::CW + k] = x[k];
             }
+            hop_recon<MU>(uh, (R)1, ln.c, acc);
+        }
+    });
+    fold(acc, sum);
+#pragma unroll
+    for (int k = 0; k < 12; ++k) rho[k] += sum[k];
+}
+// The same without LDS, every lane hopping into its own site (2^4 blocks, where half of
+// the sites lie on any direction's face): rho += the face hops into the site of parity PR.
+template <int PR, class BK, class S, class SS, class R, class P>
+__device__ __forceinline__ void gather_half(const SapArgs<S, SS, P> &a, const Lane<BK, R> &ln, const int (&g)[4],
+                                            int64_t b, const SS *dlt, const float *dlt_sc, R kappa, R (&rho)[12]) {
+    const int B[4] = {BK::bx, BK::by, BK::bz, BK::bt};
+    int l[4];
+    local_coords(B, PR, ln.s, l);
+    R acc[24], sum[12];
+#pragma unroll
+    for (int k = 0; k < 24; ++k) acc[k] = 0;
+    static_for<0, 4>([&](auto m) {
+        constexpr int MU = decltype(m)::value;
+        if (!(ln.in[PR] >> MU & 1u)) {
+            int lm[4] = {l[0], l[1], l[2], l[3]}, sg;
             lm[MU] = ln.f ? B[MU] - 1 : 0;
-            const int64_t nbp = 2 * block_index(geo.G, gn) + (1 - PR);
-            const int ns = local_half_index(B, lm);
-            const int64_t lbp = ln.f ? nbp : 2 * b + PR;
-            const int ls = ln.f ? ns : ln.s;
-            View<false> lv;
-            lv.set(reinterpret_cast<const char *>(a.links) + lbp * (NV * VS), 0);
-            Link<MU, S, VS> u;
-            u.load(lv, (unsigned)(ls * 16), ln.f != 0);
-            u.arrive(ln.f != 0);
-            R chi[24];
-            load_site<R, 24>(dlt, dlt_sc, nbp, ns, Vbh, chi);
-            hop_dir<MU>(chi, u, ln.c, kappa * sg * site_scale<R, S>(a.lscale, lbp, ls, Vbh), acc);
+            const int64_t nb = face_block<MU>(a.geo, g, ln.f, sg);
+            R uh[12];
+            const R w = face_hop<PR, MU, BK>(a, b, nb, ln.s, local_half_index(B, lm), ln.f, ln.c, kappa * (R)sg, dlt,
+                                             dlt_sc, uh);
+            hop_recon<MU>(uh, w, w * ln.c, acc);
         }
     });
     fold(acc, sum);
@@ -725,23 +880,36 @@ template <class BK, class R> __device__ __forceinline__ void block_sum3(R &a, R 
     }
 }
 
-#ifndef SAPDD_SAP_WPE32
-#define SAPDD_SAP_WPE32 4
-#endif
-#ifndef SAPDD_SAP_WPE16
-#define SAPDD_SAP_WPE16 4
-#endif
-template <class BK, class S, class R> constexpr int sap_waves_per_eu() {
-    if (BK::Vbh < 32) return sizeof(R) == 8 ? 1 : 2;
-    return sizeof(R) == 8 ? 2 : sizeof(S) == 4 ? SAPDD_SAP_WPE32 : SAPDD_SAP_WPE16;
+// Waves per SIMD the kernel is compiled for, and whether a hop loads the next direction's
+// link ahead. WIDE chooses between two forms of the FP32 kernel on 8x4^3 blocks, whose
+// workgroups have two waves per SIMD: one workgroup per CU with the look-ahead in 140
+// registers, or two without it in 128. Half-sweep times in us, wide / narrow:
+//   16^3 x 32, 1 rhs (128 workgroups)    42.3 / 46.6
+//   16^3 x 32, 12 rhs (1536)              256 / 234
+//   32^3 x 64, 4 rhs (8192)              1344 / 1262
+// On 4^4 blocks (one wave per SIMD and workgroup) the look-ahead in 140 registers wins
+// throughout (32^3 x 64, 4 rhs: 1216 / 1242); FP16 links need 128 registers either way;
+// FP64 spills less without it (16^3 x 32: 93.3 -> 85.5 us). The forms differ in register
+// use only, not in any operation, so a right-hand side gets the same bits from both.
+template <class BK, class S, class R> constexpr bool sap_two_forms() {
+    return sizeof(S) == 4 && sizeof(R) == 4 && BK::Vbh == 256;
+}
+template <class BK, class S, class R, bool WIDE> constexpr int sap_waves_per_eu() {
+    if (BK::Vbh < 32) return sizeof(R) == 8 ? 1 : 2;  // 2^4 blocks: one wave per workgroup
+    if (sizeof(R) == 8) return 2;
+    return sizeof(S) == 4 && WIDE ? 3 : 4;
+}
+template <class BK, class S, class R, bool WIDE> constexpr bool sap_look_ahead() {
+    return sizeof(R) == 4 && (WIDE || !sap_two_forms<BK, S, R>());
 }
 
 }  // namespace
 
-template <class BK, class S, class SS, class R, class P>
-__global__ __launch_bounds__((Tile<BK, R>::NT)) __attribute__((amdgpu_waves_per_eu(sap_waves_per_eu<BK, S, R>())))
+template <class BK, class S, class SS, class R, class P, bool WIDE>
+__global__ __launch_bounds__((Tile<BK, R>::NT)) __attribute__((amdgpu_waves_per_eu(sap_waves_per_eu<BK, S, R, WIDE>())))
 void sap_kernel(SapArgs<S, SS, P> a) {
     constexpr int Vbh = BK::Vbh;
+    constexpr bool AHEAD = sap_look_ahead<BK, S, R, WIDE>();
     typedef Tile<BK, R> T;
     typedef typename T::VR VR;
     __shared__ VR lds[2 * T::BUF];
@@ -809,8 +977,17 @@ void sap_kernel(SapArgs<S, SS, P> a) {
     if (a.mode >= 1) {
         int g[4];
         block_coords(geo.G, b, g);
-        gather_half<1, BK, S, SS, R>(a, ln, g, b, dlt, dlt_sc, kappa, O);
-        gather_half<0, BK, S, SS, R>(a, ln, g, b, dlt, dlt_sc, kappa, A);
+        if constexpr (T::PER > 1) {
+            gather_half<1, BK, S, SS, R>(a, ln, g, b, dlt, dlt_sc, kappa, O);
+            gather_half<0, BK, S, SS, R>(a, ln, g, b, dlt, dlt_sc, kappa, A);
+        } else {
+            face_items<1, BK, S, SS, R>(a, ln, g, b, dlt, dlt_sc, kappa, buf0);
+            face_items<0, BK, S, SS, R>(a, ln, g, b, dlt, dlt_sc, kappa, buf1);
+            __syncthreads();
+            face_sum<1>(ln, buf0, O);
+            face_sum<0>(ln, buf1, A);
+            __syncthreads();  // buf1 is written below
+        }
     }
 
     // ---- 2. O = A_o^-1 rho_o, bhat_e = rho_e + kappa H_eo A_o^-1 rho_o
@@ -822,7 +999,7 @@ void sap_kernel(SapArgs<S, SS, P> a) {
     le.load(bv, ln);
     put<BK, R>(buf1, ln, O);
     __syncthreads();
-    block_hop_half<0>(le, bv, ln, buf1, H);
+    block_hop_half<0, AHEAD>(le, bv, ln, buf1, H);
 #pragma unroll
     for (int k = 0; k < 12; ++k) {
         A[k] = fmac(kappa, H[k], A[k]);
@@ -833,16 +1010,17 @@ void sap_kernel(SapArgs<S, SS, P> a) {
     // Three barriers a step: r in buf0, A_o^-1 H_oe r in buf1, the inner products. A buffer
     // is written again only after a later barrier than its last reads.
     const R k2 = kappa * kappa;
+    P *ps = a.psi + rhs * a.psi_stride;
     for (int it = 0; it < a.nmr; ++it) {
         lo.load(bv, ln);
         put<BK, R>(buf0, ln, A);
         __syncthreads();
-        block_hop_half<1>(lo, bv, ln, buf0, H);  // odd: H_oe r
+        block_hop_half<1, AHEAD>(lo, bv, ln, buf0, H);  // odd: H_oe r
         bv.template clover<1>(ln, H, Q);         // odd: Q = A_o^-1 H_oe r
         le.load(bv, ln);
         put<BK, R>(buf1, ln, Q);
         __syncthreads();
-        block_hop_half<0>(le, bv, ln, buf1, H);  // even: H_eo Q
+        block_hop_half<0, AHEAD>(le, bv, ln, buf1, H);  // even: H_eo Q
         bv.template clover<0>(ln, A, Q);         // even: A_e r, then p = A_e r - kappa^2 H
         R pr_re = 0, pr_im = 0, pp = 0;
 #pragma unroll
@@ -880,7 +1058,6 @@ void sap_kernel(SapArgs<S, SS, P> a) {
     }
 
     // ---- 4. outputs: psi += delta (even B, odd O), keep delta and the even-site residual
-    P *ps = a.psi + rhs * a.psi_stride;
     R old[12];
     if (a.mode == 2) {
         load_half<R, P>(ps, nullptr, 2 * b, ln.s, ln.f, Vbh, H);
@@ -931,7 +1108,13 @@ static hipError_t sap_typed(const Geom &geo, const SapArgsHost &h, int colour, i
     typedef Tile<BK, R> T;
     const int64_t nblk = geo.Nd / 2, nwg = nblk * h.nact / T::PER;
     if (nblk % 8 != 0 || nwg > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((sap_kernel<BK, S, SS, R, P>), dim3((unsigned)nwg), dim3(T::NT), 0, st, a);
+    if constexpr (sap_two_forms<BK, S, R>()) {
+        if (nwg > 256) {  // more than one workgroup per CU
+            hipLaunchKernelGGL((sap_kernel<BK, S, SS, R, P, false>), dim3((unsigned)nwg), dim3(T::NT), 0, st, a);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((sap_kernel<BK, S, SS, R, P, true>), dim3((unsigned)nwg), dim3(T::NT), 0, st, a);
     return hipGetLastError();
 }
 

@@ -46,3 +46,17 @@ def test_three_kappas_share_the_waves(ctx, dims, block, nmr, prec):
         d = out[r] - ref
         assert np.linalg.norm(d) <= TOL[prec] * np.linalg.norm(ref), (r, prec)
         assert np.abs(d).max() <= 4 * TOL[prec] * np.abs(ref).max(), (r, prec)
+
+
+@pytest.mark.parametrize("prec", ["f32", "f16"])
+def test_same_bits_from_either_form_of_the_launch(ctx, prec):
+    """40 right-hand sides on 8 domains of a colour are 320 workgroups, which takes the FP32
+    kernel's form for more than one workgroup per CU; one right-hand side takes the other."""
+    dims, block = (16, 8, 8, 8), (8, 4, 4, 4)
+    f = ctx.load_gauge(synthetic.gauge_field(dims, 0.3, 83), block)
+    f.compute_clover(1.0)
+    eta = synthetic.gaussian_source(dims, 40, 84)
+    out = f.sap(0.123, eta, nmr=3, ncy=2, prec=prec)
+    for r in (0, 17, 39):
+        assert np.array_equal(out[r], f.sap(0.123, eta[r], nmr=3, ncy=2, prec=prec)), r
+    f.free()
