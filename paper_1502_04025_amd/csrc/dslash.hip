@@ -2,10 +2,11 @@
 // part M_B (the domain-internal operator of the Schwarz splitting, Sec. 3.1).
 //
 // Full operator: one thread per (site, right-hand side); neighbours are read straight
-// from global memory. Workgroups are numbered so that the nact right-hand sides of one
-// chunk of sites run back to back on the same XCD (workgroup w runs on XCD w mod 8), so
-// links and clover of the chunk are re-read from that XCD's L2 rather than from HBM, and
-// so that the chunks of one block share an XCD too.
+// from global memory. Workgroups are numbered so that the chunks of one block and right-hand
+// side, then the block's right-hand sides, follow each other on the same XCD (workgroup w
+// runs on XCD w mod 8): neighbour spinors, links and clover are then re-read from that XCD's
+// L2 rather than through the fabric. Blocks are dealt to the XCDs one by one or, for few
+// right-hand sides, in eight contiguous ranges (dslash_xcd_ranges).
 //
 // Block operator: one workgroup per (block, rhs), the block's spinor staged in LDS and
 // the hops through the block faces masked off.
@@ -48,28 +49,40 @@ template <class BK> struct GeoC {  // geometry with compile-time block extents
 constexpr int DSLASH_WG = 256;
 
 // Chunks of DSLASH_WG sites that make up one block (its even half, then its odd half):
-// they go to the same XCD, so the hops between the two halves, most of a site's
-// neighbours, find the other half in that XCD's L2.
+// they run next to each other on one XCD, so the hops between the two halves, most of a
+// site's neighbours, find the other half in that XCD's L2.
 template <class BK> constexpr int full_chunks_per_block() {
     return 2 * BK::Vbh > DSLASH_WG ? 2 * BK::Vbh / DSLASH_WG : 1;
 }
 
-
+// How blocks go to the XCDs. In eight contiguous ranges, the next blocks in x (and y) are on
+// the same XCD at about the same time and the face spinors come from its L2, as long as few
+// right-hand sides lie between them; with many, a block's own right-hand sides fill the L2
+// and dealing the blocks out one by one keeps the fabric's traffic even. FP64 operator in
+// us, one by one (block halves apart, as before) / one by one / ranges:
+//   16^3 x 32, 8x4^3, 1 rhs     72.3 / 72.7 / 53.9
+//   24^3 x 48, 4^4, 5 rhs       1116 / 1116 / 959
+//   48^3 x 96, 8x4^3, 2 rhs     8155 / 8152 / 6608
+//   32^3 x 64, 8x4^3, 6 rhs     3622 / 3752 / 3511
+//   32^3 x 64, 8x4^3, 12 rhs    6987 / 6865 / 6812   (FP32 input, with a residual: 17298 / 16650 / 17375)
+//   32^3 x 64, 4^4, 12 rhs      6611 / 6469 / 7186   (17087 / 16724 / 18202)
+static bool dslash_xcd_ranges(int nact) { return nact <= 8; }
 
 template <class BK, class S, class TI, class TO, class R>
 __global__ __launch_bounds__(DSLASH_WG) void dslash_full_kernel(Geom geo, CF<S> links, CF<S> tclov, R kappa,
                                                                  CF<TI> in, MF<TO> out, const double *sub,
                                                                  double *part, const int *active, int nact,
-                                                                 int nchunk, int ins_, int outs_, int subs_,
-                                                                 const double *kap) {
+                                                                 int nchunk, int ranges, int ins_, int outs_,
+                                                                 int subs_, const double *kap) {
     constexpr int Vbh = BK::Vbh;
     constexpr int G = full_chunks_per_block<BK>();
     const int w = blockIdx.x;
     const int xcd = w & 7;
     const int k = w >> 3;
-    const int slot = k % nact;
-    const int q = k / nact;
-    const int chunk = ((q / G) * 8 + xcd) * G + q % G;
+    const int slot = k / G % nact;
+    const int q = k / G / nact;  // group of G chunks within the XCD's share
+    const int share = (nchunk / G + 7) / 8;
+    const int chunk = (ranges ? xcd * share + q : q * 8 + xcd) * G + k % G;
     const int rhs = active ? active[slot] : slot;
     const int64_t site = (int64_t)chunk * DSLASH_WG + threadIdx.x;
     const bool valid = chunk < nchunk && site < geo.V;
@@ -179,7 +192,7 @@ static hipError_t full_typed(const Geom &geo, Fld links, Fld tclov, double kappa
     hipLaunchKernelGGL((dslash_full_kernel<BK, S, TI, TO, R>), dim3((unsigned)nwg), dim3(DSLASH_WG), 0, st, geo,
                        CF<S>{(const S *)links.data, links.scale}, CF<S>{(const S *)tclov.data, tclov.scale},
                        (R)kappa, CF<TI>{(const TI *)io.in.data, io.in.scale}, MF<TO>{(TO *)io.out.data, io.out.scale},
-                       io.sub, io.part, io.active, io.nact, nchunk, io.in_stride, io.out_stride, io.sub_stride,
+                       io.sub, io.part, io.active, io.nact, nchunk, dslash_xcd_ranges(io.nact) ? 1 : 0, io.in_stride, io.out_stride, io.sub_stride,
                        io.kappa);
     return hipGetLastError();
 }
