@@ -136,7 +136,8 @@ def roofline_sap(prof, cfg, prec, nmr):
 
 
 def dslash_bandwidth(ctx, warm=10, reps=100):
-    """Block Dslash on 32^3 x 64 (4^4 domains), FP16 and FP32 storage, device arrays:
+    """Block Dslash on 32^3 x 64 (4^4 domains), FP16 and FP32 storage, from and to the
+    caller's FP64 device arrays (one kernel):
     `warm` untimed launches, then `reps` launches each timed by its own HIP-event pair;
     GB/s at the median launch time, with p10/p90."""
     import torch
@@ -159,7 +160,7 @@ def dslash_bandwidth(ctx, warm=10, reps=100):
             f.apply_block_D(cfg["kappa"], psi, prec=prec, out=out, links12=two_row)
             ts.append(ctx.profile(False)["block_dslash"]["seconds"])
         med, p10, p90 = (float(np.percentile(ts, q)) for q in (50, 10, 90))
-        byts = pm.block_dslash_bytes(cfg["block"], prec, links12=two_row) * V
+        byts = pm.block_dslash_bytes(cfg["block"], prec, links12=two_row, io="f64") * V
         gbs = byts / med / 1e9
         kname = "dslash_block12_kernel" if two_row else "dslash_block_kernel"
         res[prec + ("_links12" if two_row else "")] = dict(

@@ -750,33 +750,28 @@ static int apply_common(sapdd_ctx *c, const sapdd_field *fc, double kappa, int p
     if (two_row) CHK(links12_copy(c, f, prec));
     const double *src;
     CHK(stage_in(c, "stage_in", in, nd, flags, &src));
-    Fld fin, fout;
-    CHK(spinor_buf(c, "op_in", g, nrhs, prec, 24, &fin));
-    CHK(spinor_buf(c, "op_out", g, nrhs, prec, 24, &fout));
-    HIPCHK(c, launch_pack(g, 24, nrhs, src, fin, c->stream));
-    if (two_row) {
-        KLAUNCH(c, SAPDD_K_BLOCK_DSLASH,
-                launch_dslash_block12(g, f->links12[prec], tclov_of(f, prec), kappa, fin, fout, nrhs, c->stream));
-    } else if (block) {
-        KLAUNCH(c, SAPDD_K_BLOCK_DSLASH, launch_dslash_block(g, links_of(f, prec), tclov_of(f, prec), kappa, fin, fout, nrhs, c->stream));
-    } else {
-        int *ident;
-        CHK(identity_list(c, nrhs, &ident));
-        DslashIO io{};
-        io.in = fin;
-        io.out = fout;
-        io.active = ident;
-        io.nact = nrhs;
-        io.in_stride = io.out_stride = io.sub_stride = 1;
-        KLAUNCH(c, SAPDD_K_DSLASH, launch_dslash_full(g, links_of(f, prec), tclov_of(f, prec), kappa, io, c->stream));
-    }
     double *dst = out;
     if (!(flags & SAPDD_DEVICE_PTRS)) {
         void *d;
         CHK(buf(c, "stage_out", nd * 8, &d));
         dst = (double *)d;
     }
-    HIPCHK(c, launch_unpack(g, 24, nrhs, fout, dst, c->stream));
+    if (two_row) {
+        KLAUNCH(c, SAPDD_K_BLOCK_DSLASH,
+                launch_dslash_block12(g, f->links12[prec], tclov_of(f, prec), kappa, src, dst, nrhs, c->stream));
+    } else if (block) {
+        KLAUNCH(c, SAPDD_K_BLOCK_DSLASH, launch_dslash_block(g, links_of(f, prec), tclov_of(f, prec), kappa, src, dst, nrhs, c->stream));
+    } else {
+        Fld fin;
+        CHK(spinor_buf(c, "op_in", g, nrhs, prec, 24, &fin));
+        HIPCHK(c, launch_pack(g, 24, nrhs, src, fin, c->stream));
+        DslashIO io{};
+        io.in = fin;
+        io.canon = dst;
+        io.nact = nrhs;
+        io.in_stride = 1;
+        KLAUNCH(c, SAPDD_K_DSLASH, launch_dslash_full(g, links_of(f, prec), tclov_of(f, prec), kappa, io, c->stream));
+    }
     if (!(flags & SAPDD_DEVICE_PTRS)) HIPCHK(c, hipMemcpyAsync(out, dst, nd * 8, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return SAPDD_OK;

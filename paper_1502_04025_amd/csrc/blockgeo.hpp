@@ -8,6 +8,7 @@
 #pragma once
 #include <utility>
 
+#include "canon.hpp"
 #include "core.hpp"
 
 namespace sapdd {
@@ -231,6 +232,37 @@ __device__ __forceinline__ void block_hop(int src, const SiteInfo &si, const LK 
         pull_dir<3, BK>(si, U, out, sp, hb);
     }
     __syncthreads();  // the next hop may only overwrite the buffer after every read
+}
+
+// LDS of a block operator kernel: the hops' exchange area, then the results on their way to
+// the canonical array.
+template <class BK, class S, class R> struct BlockLds {
+    static constexpr int hop = HopLds<BK>::PER * (int)sizeof(R), out = BK::NT * (int)sizeof(CanonSlot<S>);
+    static constexpr int bytes = hop > out ? hop : out;
+};
+template <class BK> __device__ __forceinline__ int64_t canon_index_bk(const Geom &geo, int64_t b, const int (&l)[4]) {
+    int g[4];
+    block_coords(geo.G, b, g);
+    return g[0] * BK::bx + l[0] +
+           (int64_t)geo.L[0] * (g[1] * BK::by + l[1] +
+                                (int64_t)geo.L[1] * (g[2] * BK::bz + l[2] + (int64_t)geo.L[2] * (g[3] * BK::bt + l[3])));
+}
+// The site at canonical index idx, in storage precision S.
+template <class S, class R> __device__ __forceinline__ void block_load(const double *in, int64_t idx, R (&psi)[24]) {
+    double e[24];
+    canon_load(in, idx, e);
+    round_site<S>(e, psi);
+}
+// Every thread's site (local coordinates l), rounded to storage precision S, to the canonical
+// array. The last hop's barrier has freed the exchange area.
+template <class BK, class S, class R>
+__device__ __forceinline__ void block_store(double *out, int64_t idx, const int (&l)[4], const R (&res)[24], char *lds) {
+    CanonSlot<S> *st = reinterpret_cast<CanonSlot<S> *>(lds);
+    CanonSlot<S> &slot = st[l[0] + BK::bx * (l[1] + BK::by * (l[2] + BK::bz * l[3]))];
+    slot.set(res);
+    slot.idx = idx;
+    __syncthreads();
+    canon_put<BK::NT>(out, st);
 }
 
 }  // namespace sapdd

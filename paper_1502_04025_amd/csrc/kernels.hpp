@@ -41,6 +41,8 @@ hipError_t launch_sap_clover(const Geom &geo, const double *tclov, double kappa,
 struct DslashIO {
     Fld in;            // spinor of rhs r at in + r * in_stride * V * 24 (scales: * V)
     Fld out;           // idem with out_stride
+    double *canon;     // if set: the result goes to this canonical FP64 array instead (one
+                       // array of V * 24 per slot), rounded to the links' precision
     const double *sub; // if set (FP64 out only): out = sub - M in, rhs stride sub_stride
     double *part;      // if set: per-workgroup partial |out|^2, [nact][dslash_full_partials]
     const int *active; // if set: rhs index of each of the nact slots
@@ -53,18 +55,19 @@ int dslash_full_partials(const Geom &geo);
 // out = M in over the whole lattice. links/clov in `lprec` (FP64: links + T in FP64).
 hipError_t launch_dslash_full(const Geom &geo, Fld links, Fld tclov, double kappa, const DslashIO &io,
                               hipStream_t st);
-// out = M_B in (hops between blocks dropped), one workgroup per (block, rhs).
-hipError_t launch_dslash_block(const Geom &geo, Fld links, Fld tclov, double kappa, Fld in, Fld out, int nrhs,
-                               hipStream_t st);
+// out = M_B in (hops between blocks dropped), one workgroup per (block, rhs): canonical FP64
+// arrays, rounded to the links' precision on the way in and out.
+hipError_t launch_dslash_block(const Geom &geo, Fld links, Fld tclov, double kappa, const double *in, double *out,
+                               int nrhs, hipStream_t st);
 
 // ---- block operator with two-row links (links12.hip)
 // Rows 0 and 1 of every link of the FP64 block-tiled field (48 reals per site) in out.prec
 // (P32 or P16 with per-site scales).
 hipError_t launch_links12_pack(const Geom &geo, const double *links64, Fld out, hipStream_t st);
-// out = M_B in with the links in that form (third rows rebuilt in the kernel), FP32 or
-// FP16 storage throughout.
-hipError_t launch_dslash_block12(const Geom &geo, Fld links12, Fld tclov, double kappa, Fld in, Fld out, int nrhs,
-                                 hipStream_t st);
+// out = M_B in with the links in that form (third rows rebuilt in the kernel), canonical
+// arrays in FP32 or FP16 storage precision.
+hipError_t launch_dslash_block12(const Geom &geo, Fld links12, Fld tclov, double kappa, const double *in, double *out,
+                                 int nrhs, hipStream_t st);
 
 // ---- Schwarz sweep (sap.hip)
 struct SapArgsHost {

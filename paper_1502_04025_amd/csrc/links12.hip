@@ -78,44 +78,42 @@ __global__ void links12_pack_kernel(Geom geo, const double *__restrict__ links, 
 template <class BK, class S, class R>
 __global__ __launch_bounds__(BK::NT) void dslash_block12_kernel(Geom geo, const S *links12, const float *lscale,
                                                                 const S *tclov, const float *tscale, R kappa,
-                                                                const S *in, const float *inscale, S *out,
-                                                                float *outscale) {
+                                                                const double *in, double *out) {
     constexpr int Vbh = BK::Vbh;
-    __shared__ R lds[HopLds<BK>::PER];
+    __shared__ __align__(16) char lds[BlockLds<BK, S, R>::bytes];
     const SiteInfo si = site_info<BK>(threadIdx.x);
     const int64_t b = blockIdx.x;
     const int rhs = blockIdx.y;
     const int64_t bp = 2 * b + si.p;
-    const int64_t ioff = (int64_t)rhs * geo.V * 24, soff = (int64_t)rhs * geo.V;
+    const int64_t idx = canon_index_bk<BK>(geo, b, si.l);
     constexpr bool NT = true;  // every byte is used by one workgroup only
     SiteLinks12<S, R> U;
     U.template init<NT>(links12, lscale, bp, si.s, Vbh);
     R psi[24], hop[24];
-    load_site<R, 24, S, NT>(in + ioff, inscale ? inscale + soff : nullptr, bp, si.s, Vbh, psi);
-    block_hop<BK>(0, si, U, psi, hop, lds);  // odd sites receive
-    block_hop<BK>(1, si, U, psi, hop, lds);  // even sites receive
+    block_load<S>(in + (int64_t)rhs * geo.V * 24, idx, psi);
+    block_hop<BK>(0, si, U, psi, hop, (R *)lds);  // odd sites receive
+    block_hop<BK>(1, si, U, psi, hop, (R *)lds);  // even sites receive
     R res[24];
     CloverRegs<S, R> cl;
     cl.template load<NT>(tclov, tscale, bp, si.s, Vbh);
     clover_mul(cl, psi, res, kappa);
 #pragma unroll
     for (int c = 0; c < 24; ++c) res[c] = fmac(-kappa, hop[c], res[c]);
-    store_site<R, 24, S, NT>(out + ioff, outscale ? outscale + soff : nullptr, bp, si.s, Vbh, res);
+    block_store<BK, S>(out + (int64_t)rhs * geo.V * 24, idx, si.l, res, lds);
 }
 
 template <class BK>
-hipError_t block12_shape(const Geom &geo, Fld links12, Fld tclov, double kappa, Fld in, Fld out, int nrhs,
-                         hipStream_t st) {
-    if (links12.prec != in.prec || in.prec != out.prec || tclov.prec != links12.prec) return hipErrorInvalidValue;
+hipError_t block12_shape(const Geom &geo, Fld links12, Fld tclov, double kappa, const double *in, double *out,
+                         int nrhs, hipStream_t st) {
+    if (tclov.prec != links12.prec) return hipErrorInvalidValue;
     const dim3 grid((unsigned)geo.Nd, (unsigned)nrhs);
     if (links12.prec == P32)
         hipLaunchKernelGGL((dslash_block12_kernel<BK, float, float>), grid, dim3(BK::NT), 0, st, geo,
-                           (const float *)links12.data, nullptr, (const float *)tclov.data, nullptr, (float)kappa,
-                           (const float *)in.data, nullptr, (float *)out.data, nullptr);
+                           (const float *)links12.data, nullptr, (const float *)tclov.data, nullptr, (float)kappa, in, out);
     else if (links12.prec == P16)
         hipLaunchKernelGGL((dslash_block12_kernel<BK, half_t, float>), grid, dim3(BK::NT), 0, st, geo,
                            (const half_t *)links12.data, links12.scale, (const half_t *)tclov.data, tclov.scale,
-                           (float)kappa, (const half_t *)in.data, in.scale, (half_t *)out.data, out.scale);
+                           (float)kappa, in, out);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();
@@ -137,8 +135,8 @@ hipError_t launch_links12_pack(const Geom &geo, const double *links64, Fld out, 
     return hipGetLastError();
 }
 
-hipError_t launch_dslash_block12(const Geom &geo, Fld links12, Fld tclov, double kappa, Fld in, Fld out, int nrhs,
-                                 hipStream_t st) {
+hipError_t launch_dslash_block12(const Geom &geo, Fld links12, Fld tclov, double kappa, const double *in,
+                                 double *out, int nrhs, hipStream_t st) {
     if (nrhs <= 0 || geo.Nd == 0) return hipSuccess;
     if (geo.B[0] == 2 && geo.B[1] == 2 && geo.B[2] == 2 && geo.B[3] == 2)
         return block12_shape<Blk<2, 2, 2, 2>>(geo, links12, tclov, kappa, in, out, nrhs, st);

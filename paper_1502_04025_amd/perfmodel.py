@@ -41,11 +41,12 @@ def internal_fraction(block) -> float:
 LINK12_BYTES = {"f32": 192, "f16": 100}
 
 
-def block_dslash_bytes(block, prec: str, nrhs: int = 1, links12: bool = False) -> float:
-    """Block operator M_B: internal links, clover, one spinor read and one written."""
+def block_dslash_bytes(block, prec: str, nrhs: int = 1, links12: bool = False, io: str | None = None) -> float:
+    """Block operator M_B: internal links, clover, one spinor read and one written, in
+    precision `io` (the library's kernel: "f64", the caller's arrays; default: prec)."""
     f = internal_fraction(block)
     lb = LINK12_BYTES[prec] if links12 else LINK_BYTES[prec]
-    return f * lb + CLOVER_BYTES[prec] + 2 * nrhs * SPINOR_BYTES[prec]
+    return f * lb + CLOVER_BYTES[prec] + 2 * nrhs * SPINOR_BYTES[io or prec]
 
 
 def block_dslash_flops(block) -> float:
