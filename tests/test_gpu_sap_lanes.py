@@ -60,3 +60,31 @@ def test_same_bits_from_either_form_of_the_launch(ctx, prec):
     for r in (0, 17, 39):
         assert np.array_equal(out[r], f.sap(0.123, eta[r], nmr=3, ncy=2, prec=prec)), r
     f.free()
+
+
+@pytest.mark.parametrize("dims,block", [((4, 4, 4, 4), (2, 2, 2, 2)), ((8, 8, 8, 8), (4, 4, 4, 4))])
+def test_clover_inverse_with_row_exchanges(ctx, dims, block):
+    """The 6x6 inverses where pivoting matters: a clover term that puts 1e-3 on the diagonal of
+    1 + kappa T beside off-diagonal entries of order one. The bound is rounding times the
+    condition number (below 1e5 here) times the few operations per entry: 1e-10."""
+    kappa = 0.12
+    lead = dims[::-1]
+    rng = np.random.default_rng(85)
+    t = np.zeros(lead + (12, 12), dtype=np.complex128)
+    for k in range(2):
+        g = rng.standard_normal(lead + (6, 6)) + 1j * rng.standard_normal(lead + (6, 6))
+        h = g + np.conj(np.swapaxes(g, -1, -2))
+        i = np.arange(6)
+        h[..., i, i] = (1e-3 - 1.0) / kappa
+        off = ~np.eye(6, dtype=bool)
+        h[..., off] /= kappa
+        t[..., 6 * k:6 * k + 6, 6 * k:6 * k + 6] = h
+    assert np.linalg.cond(np.eye(12) + kappa * t).max() < 1e5
+    u = synthetic.gauge_field(dims, 0.3, 86)
+    eta = synthetic.gaussian_source(dims, 1, 87)
+    f = ctx.load_gauge(u, block)
+    f.load_clover(t)
+    out = f.sap(kappa, eta, nmr=1, ncy=1, prec="f64")
+    f.free()
+    ref = osap.sap(osap.BlockSystem(u, t, kappa, block), eta[0], 1, 1)
+    assert np.linalg.norm(out[0] - ref) <= 1e-10 * np.linalg.norm(ref)
