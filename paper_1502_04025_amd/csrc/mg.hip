@@ -27,6 +27,7 @@
 // least squares problem at the end of a cycle, and the cycle's correction is added to
 // the coarse solution, whose residual starts the next.
 #include "kernels.hpp"
+#include "lanes.hpp"
 
 namespace sapdd {
 
@@ -210,44 +211,66 @@ int mg_colour_of(const int g[4], const MgColouring &cl) { return mg_colour(g, cl
 
 // ---------------------------------------------------------------- fine-grid kernels
 
+// Aggregate and system slot of a workgroup: workgroup w runs on XCD w mod 8, and the
+// systems of one aggregate follow each other there, so that its part of P is read from
+// that XCD's L2 by all but the first. The number of aggregates is a multiple of 16 (the
+// block grid is even in every direction).
+__device__ __forceinline__ int64_t mg_aggregate(int nact, int &slot) {
+    const int w = blockIdx.x, k = w >> 3;
+    slot = k % nact;
+    return (int64_t)(k / nact) * 8 + (w & 7);
+}
+
 // out(rhs)[b][k] = (P^H in(rhs))(b)[k] for one aggregate b per workgroup. in: FP64
 // block-tiled spinors of the listed rhs at in + rhs * in_stride; out FP32 complex at
-// out + rhs * out_stride. FP64 accumulation.
+// out + rhs * out_stride. FP64 accumulation. Bound by reading P; the sums over a wave halve
+// their values with every step (wave_scatter), where a butterfly of each of the 2 NV
+// values through LDS shuffles took most of the time. 16^3 x 32, 16 vectors, 4 systems, one
+// application (this, the prolongation and the update of psi): 347 -> 187 us.
 template <int NV>
 __global__ __launch_bounds__(512) void mg_restrict_kernel(const double *in, int64_t in_stride, const float *P,
                                                            int64_t V, int Vbh, float2 *out, int64_t out_stride,
-                                                           const int *active) {
-    __shared__ double lds[8 * 2 * NV];
+                                                           const int *active, int nact) {
+    constexpr int N = NV <= 2 ? 4 : NV <= 4 ? 8 : NV <= 8 ? 16 : 32;  // 2 NV rounded up
+    __shared__ double lds[2][8][N];
     const int tid = threadIdx.x;
     const bool act = tid < 2 * Vbh;
     const int p = act ? tid / Vbh : 0, s = act ? tid % Vbh : 0;
-    const int64_t b = blockIdx.x, bp = 2 * b + p;
-    const int rhs = active ? active[blockIdx.y] : (int)blockIdx.y;
+    int slot;
+    const int64_t b = mg_aggregate(nact, slot), bp = 2 * b + p;
+    const int rhs = active ? active[slot] : slot;
     const double *r = in + (int64_t)rhs * in_stride;
-    float2 *o = out + (int64_t)rhs * out_stride + b * (2 * NV);
+#pragma unroll
     for (int ch = 0; ch < 2; ++ch) {
         dv2 x[6];
 #pragma unroll
         for (int c = 0; c < 6; ++c) x[c] = act ? ld64(r, bp, 6 * ch + c, s, Vbh) : dv2{0.0, 0.0};
-        double acc[2 * NV];
+        double acc[N];
 #pragma unroll
-        for (int j = 0; j < NV; ++j) {
-            float pr[6], pi[6];
-            if (act) ldP(P + (int64_t)j * V * 24, bp, ch, s, Vbh, pr, pi);
-            double are = 0, aim = 0;
+        for (int j = 0; j < N / 2; ++j) {
+            acc[2 * j] = acc[2 * j + 1] = 0.0;
+            if (j < NV) {
+                float pr[6], pi[6];
+                ldP(P + (int64_t)j * V * 24, bp, ch, s, Vbh, pr, pi);
 #pragma unroll
-            for (int c = 0; c < 6; ++c) {
-                const double qr = act ? (double)pr[c] : 0.0, qi = act ? (double)pi[c] : 0.0;
-                are += qr * x[c].x + qi * x[c].y;
-                aim += qr * x[c].y - qi * x[c].x;
+                for (int c = 0; c < 6; ++c) {
+                    acc[2 * j] += (double)pr[c] * x[c].x + (double)pi[c] * x[c].y;
+                    acc[2 * j + 1] += (double)pr[c] * x[c].y - (double)pi[c] * x[c].x;
+                }
             }
-            acc[2 * j] = are;
-            acc[2 * j + 1] = aim;
         }
-        wg_sum<2 * NV>(acc, lds);
-        if (tid == 0)
-#pragma unroll
-            for (int j = 0; j < NV; ++j) o[ch * NV + j] = make_float2((float)acc[2 * j], (float)acc[2 * j + 1]);
+        wave_scatter<N>(acc);
+        lds[ch][tid >> 6][wave_scatter_index<N>(tid & 63)] = acc[0];  // the same value from each of its lanes
+    }
+    __syncthreads();
+    if (tid < 2 * NV) {  // coarse index tid = ch * NV + j
+        const int ch = tid / NV, j = tid % NV, nw = blockDim.x >> 6;
+        double re = 0, im = 0;
+        for (int q = 0; q < nw; ++q) {
+            re += lds[ch][q][2 * j];
+            im += lds[ch][q][2 * j + 1];
+        }
+        out[(int64_t)rhs * out_stride + b * (2 * NV) + tid] = make_float2((float)re, (float)im);
     }
 }
 
@@ -268,15 +291,16 @@ struct MgCoarseSrc {
 
 template <int NV>
 __global__ __launch_bounds__(512) void mg_prolong_kernel(MgCoarseSrc src, const float *P, Geom geo, double *out,
-                                                          int64_t out_stride, const int *active) {
+                                                          int64_t out_stride, const int *active, int nact) {
     constexpr int K = 2 * NV;
     __shared__ float2 e[K];
     const int tid = threadIdx.x;
     const int Vbh = geo.Vbh;
     const bool act = tid < 2 * Vbh;
     const int p = act ? tid / Vbh : 0, s = act ? tid % Vbh : 0;
-    const int64_t b = blockIdx.x, bp = 2 * b + p;
-    const int rhs = active ? active[blockIdx.y] : (int)blockIdx.y;
+    int slot;
+    const int64_t b = mg_aggregate(nact, slot), bp = 2 * b + p;
+    const int rhs = active ? active[slot] : slot;
     if (tid < K) {
         float2 v = make_float2(0.f, 0.f);
         if (src.q >= 0) {
@@ -323,16 +347,18 @@ template <int NV>
 static hipError_t restrict_nv(const Geom &geo, const double *in, int64_t in_stride, const float *P, float2 *out,
                               int64_t out_stride, const int *active, int nact, hipStream_t st) {
     const int nt = (2 * geo.Vbh + 63) / 64 * 64;
-    hipLaunchKernelGGL(mg_restrict_kernel<NV>, dim3((unsigned)geo.Nd, (unsigned)nact), dim3(nt), 0, st, in,
-                       in_stride, P, geo.V, geo.Vbh, out, out_stride, active);
+    if (geo.Nd % 8 != 0 || geo.Nd * nact > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(mg_restrict_kernel<NV>, dim3((unsigned)(geo.Nd * nact)), dim3(nt), 0, st, in,
+                       in_stride, P, geo.V, geo.Vbh, out, out_stride, active, nact);
     return hipGetLastError();
 }
 template <int NV>
 static hipError_t prolong_nv(const Geom &geo, const MgCoarseSrc &src, const float *P, double *out,
                              int64_t out_stride, const int *active, int nact, hipStream_t st) {
     const int nt = (2 * geo.Vbh + 63) / 64 * 64;
-    hipLaunchKernelGGL(mg_prolong_kernel<NV>, dim3((unsigned)geo.Nd, (unsigned)nact), dim3(nt), 0, st, src, P, geo,
-                       out, out_stride, active);
+    if (geo.Nd % 8 != 0 || geo.Nd * nact > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(mg_prolong_kernel<NV>, dim3((unsigned)(geo.Nd * nact)), dim3(nt), 0, st, src, P, geo,
+                       out, out_stride, active, nact);
     return hipGetLastError();
 }
 

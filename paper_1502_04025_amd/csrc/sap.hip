@@ -55,6 +55,7 @@
 // X = A_o^-1 - 1 on odd sites (A_o^-1 = 1 + X).
 #include "blockgeo.hpp"
 #include "kernels.hpp"
+#include "lanes.hpp"
 
 namespace sapdd {
 
@@ -83,47 +84,6 @@ template <class S, class SS, class P> struct SapArgs {  // S: links and clover, 
 namespace {
 
 // ------------------------------------------------------------------ lanes
-// Other lane's register contents: the DPP control moves inside rows of 16 lanes.
-template <int CTRL> __device__ __forceinline__ float dpp_move(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
-}
-template <int CTRL> __device__ __forceinline__ double dpp_move(double v) {
-    int2 x = __builtin_bit_cast(int2, v);
-    x.x = __builtin_amdgcn_update_dpp(0, x.x, CTRL, 0xF, 0xF, false);
-    x.y = __builtin_amdgcn_update_dpp(0, x.y, CTRL, 0xF, 0xF, false);
-    return __builtin_bit_cast(double, x);
-}
-__device__ __forceinline__ float lane_value(float v, int lane) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
-}
-__device__ __forceinline__ double lane_value(double v, int lane) {
-    int2 x = __builtin_bit_cast(int2, v);
-    x.x = __builtin_amdgcn_readlane(x.x, lane);
-    x.y = __builtin_amdgcn_readlane(x.y, lane);
-    return __builtin_bit_cast(double, x);
-}
-
-// (a, b) -> a = { a of lanes 0-31, b of lanes 0-31 }, b = { a of lanes 32-63, b of lanes
-// 32-63 }: the upper half of a and the lower half of b change places.
-__device__ __forceinline__ void swap32(unsigned &a, unsigned &b) {
-    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-    a = r[0];
-    b = r[1];
-}
-__device__ __forceinline__ void swap32(float &a, float &b) {
-    unsigned x = __builtin_bit_cast(unsigned, a), y = __builtin_bit_cast(unsigned, b);
-    swap32(x, y);
-    a = __builtin_bit_cast(float, x);
-    b = __builtin_bit_cast(float, y);
-}
-__device__ __forceinline__ void swap32(double &a, double &b) {
-    uint2 x = __builtin_bit_cast(uint2, a), y = __builtin_bit_cast(uint2, b);
-    swap32(x.x, y.x);
-    swap32(x.y, y.y);
-    a = __builtin_bit_cast(double, x);
-    b = __builtin_bit_cast(double, y);
-}
-
 // Sum over the lanes of one block (GROUP = 64: the whole wave; GROUP = 8: lanes 8 g .. 8 g
 // + 7 and the same lanes + 32) in a fixed order, the same on each of them. Register to
 // register: DPP adds inside rows of 16 lanes, then the rows' sums.
