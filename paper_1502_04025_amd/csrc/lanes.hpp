@@ -55,45 +55,52 @@ __device__ __forceinline__ void swap16(double &a, double &b) {
     b = __builtin_bit_cast(double, make_uint2(r[1], t[1]));
 }
 
-// Sums of N values (a power of two, 4..32) over the 64 lanes, in a fixed order: every
-// step halves the values a lane carries and doubles the lanes behind each, so that N values
-// cost about N adds instead of 6 N. Afterwards v[0] of lane l is the total of value
-// wave_scatter_index<N>(l).
+// Sums of N values (a power of two) over the lanes of each half of a wave (N = 1..16) or over
+// the whole wave (N = 2..32), in a fixed order that does not depend on N: every step halves the
+// values a lane carries and doubles the lanes behind each, so that N values cost about N
+// adds instead of 5 or 6 N. Afterwards v[0] of lane l is the total of value
+// half_scatter_index<N>(l) (of l's half) or wave_scatter_index<N>(l); the 32 / N or 64 / N
+// lanes that differ in the low bits alone hold the same.
 template <int CTRL, int H, class V> __device__ __forceinline__ void scatter_dpp(V &v, bool upper) {
+    if constexpr (H == 0) {  // one value left: every lane adds its partner's
+        v[0] += dpp_move<CTRL>(v[0]);
+    } else {
 #pragma unroll
-    for (int k = 0; k < H; ++k) {
-        const double keep = upper ? v[k + H] : v[k], give = upper ? v[k] : v[k + H];
-        v[k] = keep + dpp_move<CTRL>(give);
+        for (int k = 0; k < H; ++k) {
+            const double keep = upper ? v[k + H] : v[k], give = upper ? v[k] : v[k + H];
+            v[k] = keep + dpp_move<CTRL>(give);
+        }
     }
 }
-template <int N> __device__ __forceinline__ void wave_scatter(double (&v)[N]) {
+template <int N, class V> __device__ __forceinline__ void half_scatter(V &v) {
     const int l = threadIdx.x & 63;
+    if constexpr (N == 1) {
+        double a = v[0], b = v[0];
+        swap16(a, b);
+        v[0] = a + b;
+    }
+#pragma unroll
+    for (int k = 0; k < N / 2; ++k) {
+        swap16(v[k], v[k + N / 2]);
+        v[k] += v[k + N / 2];
+    }
+    // the partner lanes: rotation by 8 in a row, mirror in 8 lanes, lane ^ 2, lane ^ 1
+    scatter_dpp<0x128, N / 4>(v, l & 8);
+    scatter_dpp<0x141, N / 8>(v, l & 4);
+    scatter_dpp<0x4E, N / 16>(v, l & 2);
+    scatter_dpp<0xB1, 0>(v, false);
+}
+template <int N> __device__ __forceinline__ int half_scatter_index(int l) {
+    return (l & 31) / (32 / N);  // the upper bits of l, the highest first
+}
+template <int N, class V> __device__ __forceinline__ void wave_scatter(V &v) {
 #pragma unroll
     for (int k = 0; k < N / 2; ++k) {
         swap32(v[k], v[k + N / 2]);
         v[k] += v[k + N / 2];
     }
-#pragma unroll
-    for (int k = 0; k < N / 4; ++k) {
-        swap16(v[k], v[k + N / 4]);
-        v[k] += v[k + N / 4];
-    }
-    // the partner lanes of the last steps: rotation by 8 in a row, mirror in 8 lanes, then
-    // lane ^ 2 and lane ^ 1
-    if constexpr (N >= 8) scatter_dpp<0x128, N / 8>(v, l & 8);
-    else v[0] += dpp_move<0x128>(v[0]);
-    if constexpr (N >= 16) scatter_dpp<0x141, N / 16>(v, l & 4);
-    else v[0] += dpp_move<0x141>(v[0]);
-    if constexpr (N >= 32) scatter_dpp<0x4E, N / 32>(v, l & 2);
-    else v[0] += dpp_move<0x4E>(v[0]);
-    v[0] += dpp_move<0xB1>(v[0]);
+    half_scatter<N / 2>(v);
 }
-template <int N> __device__ __forceinline__ int wave_scatter_index(int l) {
-    int k = (l >> 5 & 1) * (N / 2) + (l >> 4 & 1) * (N / 4);
-    if (N >= 8) k += (l >> 3 & 1) * (N / 8);
-    if (N >= 16) k += (l >> 2 & 1) * (N / 16);
-    if (N >= 32) k += l >> 1 & 1;
-    return k;
-}
+template <int N> __device__ __forceinline__ int wave_scatter_index(int l) { return (l & 63) / (64 / N); }
 
 }  // namespace sapdd

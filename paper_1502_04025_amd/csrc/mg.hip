@@ -499,17 +499,26 @@ __device__ __forceinline__ double wave_sum_parts(const double *part, int n) {
     return t;
 }
 
-// The totals of nval <= 2 MG_IMAX values (value v's n partials at part + v * pstride)
-// into h[v] in LDS in a fixed order: value v by wave v mod NW (blockDim.x = 64 NW), whose
-// lane l adds partials l, l + 64, ... (the loads of 256 partials in flight together),
-// then one butterfly per value; then a barrier.
-template <int NW, int NV = 2 * MG_IMAX>
-__device__ __forceinline__ void load_totals(const double *part, int64_t pstride, int n, int nval, double *h) {
-    constexpr int PER = (NV + NW - 1) / NW;  // nval <= NV
+// The totals of nval <= NV values (value v's n partials at part + v * pstride) in a fixed
+// order: value v by wave v mod NW (blockDim.x = 64 NW), whose lane l adds partials l, l + 64,
+// ... (the loads of 256 partials in flight together), then the sums over the lanes
+// (wave_scatter). put(v, total) is called once per value v < NV (zero from nval on), by a lane
+// whose totals_value is v; then a barrier.
+template <int NW, int NV> struct Totals {
+    static constexpr int PER = (NV + NW - 1) / NW;  // values of a wave
+    static constexpr int N = PER <= 4 ? 4 : PER <= 8 ? 8 : 16;
+    static_assert(PER <= 16);
+};
+template <int NW, int NV> __device__ __forceinline__ int totals_value() {
+    return (threadIdx.x >> 6) + NW * wave_scatter_index<Totals<NW, NV>::N>(threadIdx.x);
+}
+template <int NW, int NV, class PUT>
+__device__ __forceinline__ void load_totals(const double *part, int64_t pstride, int n, int nval, PUT put) {
+    constexpr int PER = Totals<NW, NV>::PER, N = Totals<NW, NV>::N;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    double acc[PER];
+    double acc[N];
 #pragma unroll
-    for (int u = 0; u < PER; ++u) acc[u] = 0.0;
+    for (int u = 0; u < N; ++u) acc[u] = 0.0;
     for (int q0 = 0; q0 < n; q0 += 4 * 64) {
         // every load unconditional, so that all are in flight together: an index out of
         // range reads partial 0 of value 0 (written and finite) and adds it times zero,
@@ -532,14 +541,17 @@ __device__ __forceinline__ void load_totals(const double *part, int64_t pstride,
                 acc[u] += x[qq][u] * (q < n && w + NW * u < nval ? 1.0 : 0.0);
             }
     }
-#pragma unroll
-    for (int u = 0; u < PER; ++u)
-        if (w + NW * u < nval) {
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) acc[u] += __shfl_xor(acc[u], off, 64);
-            if (lane == 0) h[w + NW * u] = acc[u];
-        }
+    wave_scatter<N>(acc);
+    const int v = totals_value<NW, NV>();
+    if (lane % (64 / N) == 0 && v < NV) put(v, v < nval ? acc[0] : 0.0);
     __syncthreads();
+}
+
+// Sum over the lanes of a wave, in every lane.
+__device__ __forceinline__ double wave_total(double v) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
 }
 
 __device__ __forceinline__ double *pd_of(const MgGmres &G, int rhs, int pass) {
@@ -630,142 +642,207 @@ __global__ __launch_bounds__(MG_GWG) void mg_cinit_kernel(MgGmres G) {
     wg_sum_store<1>(n, lds, 1, pn_of(G, rhs, 0) + blockIdx.x, 1);
 }
 
-// Arnoldi step j, pass 0: w = D_c (s_j v_j) into basis slot j + 1 and the partials of
-// <v_i, w>, i <= j (the Gram-Schmidt kernel applies s_i to their totals). s_j = 1 / |v_j|
-// from the norm partials of v_j. Every thread issues its stencil loads and the rows of
-// its two basis vectors (i = g and g + MG_AGRP) at once; after one barrier each thread
-// sums its row of w from the column groups' parts, and each group's two dot products
-// are summed over the 32 rows by a half-wave butterfly.
-__global__ __launch_bounds__(MG_AWG) __attribute__((amdgpu_waves_per_eu(1, 4))) void mg_capply_kernel(MgGmres G,
-                                                                                                      int j) {
-    __shared__ double ys[2][MG_AGRP][MG_ALANES];
-    const int rhs = G.active[blockIdx.y];
-    const int K = G.K;
+// Entry e of the nine blocks of a workgroup's aggregates: row of a coarse vector (a stored
+// one where there is none).
+__device__ __forceinline__ int64_t coarse_entry_row(const MgGmres &G, int e) {
+    const int K = G.K, ta = MG_ALANES / K > 0 ? MG_ALANES / K : 1;
+    // entry e: (aggregate bl, neighbour block d, row c)
+    const int bl = e / (9 * K), rem = e - bl * 9 * K, d = rem / K, c = rem - d * K;
+    const int64_t b = (int64_t)blockIdx.x * ta + bl;
+    if (!(bl < ta && b < G.Nd)) return 0;
+    // neighbour d without indexing the grid by a per-thread direction
+    const int gg[4] = {G.grid[0], G.grid[1], G.grid[2], G.grid[3]};
+    int gc[4], hc[4];
+    block_coords(gg, b, gc);
+    const int mu = (d - 1) >> 1;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const int up = gc[m] + 1 == gg[m] ? 0 : gc[m] + 1, dn = gc[m] == 0 ? gg[m] - 1 : gc[m] - 1;
+        hc[m] = d > 0 && m == mu ? ((d & 1) ? up : dn) : gc[m];
+    }
+    return block_index(gg, hc) * K + c;
+}
+
+// Arnoldi step j: w = D_c (s_j v_j) into basis slot j + 1 and the partials of <v_i, w>,
+// i <= j (the Gram-Schmidt kernel applies s_i to their totals). s_j = 1 / |v_j| from the norm
+// partials of v_j. A workgroup takes NS of the listed systems: its stencil entries are
+// loaded once for all of them, every load of a thread (18 entries, its vectors' rows at the
+// nine blocks, the rows of two basis vectors i = g and g + MG_AGRP) before the sums. The
+// vectors pass through LDS in FP64; wave n sums the column groups' parts of system n, which
+// all threads read back for their dot products. Bound by latency (one pass of a few dependent
+// loads and three barriers) and by the stencil's 19 MB from L2. The sums of a system do not
+// depend on NS or on the other systems. 16^3 x 32, 8x4^3
+// aggregates, K = 32, 4 systems: 16.4 us with a workgroup per system, 8.9 us.
+template <int NS>
+__global__ __launch_bounds__(MG_AWG) __attribute__((amdgpu_waves_per_eu(1, 2))) void mg_capply_kernel(MgGmres G,
+                                                                                                      int j, int nact) {
+    constexpr int NE = 9 * MG_ALANES;  // LDS entries: 9 blocks x 32 rows
+    static_assert(NE <= MG_AWG && NS <= MG_AWG / 64);
+    __shared__ double2 xs[NS][NE];
+    __shared__ double ys[NS][2][MG_AGRP][MG_ALANES];
+    __shared__ float wl[NS][MG_ALANES][2];
+    const int K = G.K, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const CoarseRow w(G);
-    const float2 *vb = G.basis + (int64_t)rhs * G.bstride;
-    const float2 *vj = vb + (int64_t)j * G.vstride;
-    float2 *wout = const_cast<float2 *>(vb) + (int64_t)(j + 1) * G.vstride;
-    // unconditional loads with clamped indices: for i > j or a missing row they read a
-    // stored row whose products are not kept
+    int sys[NS];  // past the list: its last system again, nothing of which is stored
+#pragma unroll
+    for (int n = 0; n < NS; ++n) {
+        const int slot = (int)blockIdx.y * NS + n;
+        sys[n] = G.active[slot < nact ? slot : nact - 1];
+    }
+    // ---- loads (unconditional, with clamped indices)
+    float2 m[9][MG_CPG];
+    {
+        const int64_t bb = w.act ? w.b : 0;
+#pragma unroll
+        for (int d = 0; d < 9; ++d)
+#pragma unroll
+            for (int t = 0; t < MG_CPG; ++t) {
+                const int c = w.g + MG_AGRP * t;
+                m[d][t] = G.Dc[((bb * 9 + d) * K + (c < K ? c : 0)) * K + w.a];
+            }
+    }
+    const int64_t erow = threadIdx.x < NE ? coarse_entry_row(G, threadIdx.x) : 0;
     const int64_t row = w.act ? w.b * K + w.a : 0;
-    float2 v[2];
+    float2 xe[NS], v[NS][2];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int i = w.g + MG_AGRP * u;
-        v[u] = vb[(int64_t)(i <= j ? i : j) * G.vstride + row];
-    }
-    // |v_j|^2 by every wave (fixed order, as wave_sum_parts): partial `lane` loaded with
-    // the stencil (clamped, times zero past nwc), the rest and the butterfly after it
-    const double *pnj = pn_of(G, rhs, j);
-    const int lane = threadIdx.x & 63;
+    for (int n = 0; n < NS; ++n) xe[n] = G.basis[(int64_t)sys[n] * G.bstride + (int64_t)j * G.vstride + erow];
+#pragma unroll
+    for (int n = 0; n < NS; ++n)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int i = w.g + MG_AGRP * u;
+            v[n][u] = G.basis[(int64_t)sys[n] * G.bstride + (int64_t)(i <= j ? i : j) * G.vstride + row];
+        }
+    // wave n: |v_j|^2 of system n from partials lane, lane + 64, ... (clamped, times zero
+    // past nwc), the first with the other loads
+    int mine = sys[0];
+#pragma unroll
+    for (int n = 1; n < NS; ++n) mine = wave == n ? sys[n] : mine;
+    const double *pnj = pn_of(G, mine, j);
     double nj = pnj[lane < G.nwc ? lane : 0] * (lane < G.nwc ? 1.0 : 0.0);
-    double yr = 0, yi = 0;  // this thread's part of (D_c v_j) row a of aggregate b
-    if (w.act) coarse_row_part(G, w, vj, yr, yi);
-    ys[0][w.g][w.r] = yr;
-    ys[1][w.g][w.r] = yi;
-    for (int q = lane + 64; q < G.nwc; q += 64) nj += pnj[q];
+    __builtin_amdgcn_sched_barrier(0);  // keep every load ahead of the sums
+    if (threadIdx.x < NE)
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) nj += __shfl_xor(nj, off, 64);
+        for (int n = 0; n < NS; ++n) xs[n][threadIdx.x] = make_double2(xe[n].x, xe[n].y);
     __syncthreads();
-    const double sj = nj > 0 ? 1.0 / sqrt(nj) : 0.0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        G.sc[(int64_t)rhs * (MG_IMAX + 1) + j] = sj;
-        const double h = sqrt(nj > 0 ? nj : 0.0);
-        if (j == 0) {
-            G.beta[rhs] = h;
-        } else {  // h_{j,j-1}
-            double *Hc = G.H + (int64_t)rhs * (MG_IMAX + 1) * MG_IMAX * 2 + 2 * (int64_t)(j - 1) * (MG_IMAX + 1);
-            Hc[2 * j] = h;
-            Hc[2 * j + 1] = 0.0;
+    // ---- columns g, g + MG_AGRP of the nine blocks, in block and column order
+    const int x0 = (w.r / K < MG_ALANES / K ? w.r / K : 0) * 9 * K;
+    double yr[NS], yi[NS];
+#pragma unroll
+    for (int n = 0; n < NS; ++n) yr[n] = yi[n] = 0.0;
+#pragma unroll
+    for (int d = 0; d < 9; ++d)
+#pragma unroll
+        for (int t = 0; t < MG_CPG; ++t) {
+            const int c = w.g + MG_AGRP * t;
+            const float f = c < K ? 1.f : 0.f;
+            const double mr = (double)(m[d][t].x * f), mi = (double)(m[d][t].y * f);
+#pragma unroll
+            for (int n = 0; n < NS; ++n) {
+                const double2 xv = xs[n][x0 + d * K + (c < K ? c : 0)];
+                yr[n] += mr * xv.x - mi * xv.y;
+                yi[n] += mr * xv.y + mi * xv.x;
+            }
+        }
+#pragma unroll
+    for (int n = 0; n < NS; ++n) {
+        ys[n][0][w.g][w.r] = yr[n];
+        ys[n][1][w.g][w.r] = yi[n];
+    }
+    __syncthreads();
+    // ---- wave n: row lane % 32 of system n, real parts in the lower half of the lanes
+    if (wave < NS) {
+        for (int q = lane + 64; q < G.nwc; q += 64) nj += pnj[q];
+        nj = wave_total(nj);
+        const double sj = nj > 0 ? 1.0 / sqrt(nj) : 0.0;
+        double y = 0;
+#pragma unroll
+        for (int q = 0; q < MG_AGRP; ++q) y += ys[wave][lane >> 5][q][w.r];
+        const float yf = w.act ? (float)(y * sj) : 0.f;
+        wl[wave][w.r][lane >> 5] = yf;
+        if ((int)blockIdx.y * NS + wave < nact) {
+            if (w.act)
+                reinterpret_cast<float *>(G.basis + (int64_t)mine * G.bstride + (int64_t)(j + 1) * G.vstride +
+                                          row)[lane >> 5] = yf;
+            if (blockIdx.x == 0 && lane == 0) {
+                G.sc[(int64_t)mine * (MG_IMAX + 1) + j] = sj;
+                const double h = sqrt(nj > 0 ? nj : 0.0);
+                if (j == 0) {
+                    G.beta[mine] = h;
+                } else {  // h_{j,j-1}
+                    double *Hc = G.H + (int64_t)mine * (MG_IMAX + 1) * MG_IMAX * 2 + 2 * (int64_t)(j - 1) * (MG_IMAX + 1);
+                    Hc[2 * j] = h;
+                    Hc[2 * j + 1] = 0.0;
+                }
+            }
         }
     }
-    coarse_row_total(ys, w.r, yr, yi);
-    yr *= sj;
-    yi *= sj;
-    if (w.act) {
-        const float2 wf = make_float2((float)yr, (float)yi);
-        if (w.g == 0) wout[w.b * K + w.a] = wf;
-        yr = wf.x;  // the dot products see the stored vector
-        yi = wf.y;
-    } else {
-        yr = yi = 0;
+    __syncthreads();
+    // ---- <v_i, w> over the 32 rows of this group, w as stored
+    double dot[4 * NS];
+#pragma unroll
+    for (int n = 0; n < NS; ++n) {
+        const double ar = wl[n][w.r][0], ai = wl[n][w.r][1];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            dot[4 * n + 2 * u] = (double)v[n][u].x * ar + (double)v[n][u].y * ai;
+            dot[4 * n + 2 * u + 1] = (double)v[n][u].x * ai - (double)v[n][u].y * ar;
+        }
     }
+    half_scatter<4 * NS>(dot);
+    const int k = half_scatter_index<4 * NS>(lane), n = k >> 2, i = w.g + MG_AGRP * (k >> 1 & 1);
+    if (w.r % (8 / NS) == 0 && i <= j && (int)blockIdx.y * NS + n < nact) {
+        int rhs = sys[0];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int i = w.g + MG_AGRP * u;
-        double pr = (double)v[u].x * yr + (double)v[u].y * yi;
-        double pi = (double)v[u].x * yi - (double)v[u].y * yr;
-#pragma unroll
-        for (int off = MG_ALANES / 2; off > 0; off >>= 1) {  // the 32 rows of this group
-            pr += __shfl_xor(pr, off, 64);
-            pi += __shfl_xor(pi, off, 64);
-        }
-        if (w.r == 0 && i <= j) {
-            double *pd = pd_of(G, rhs, 0) + blockIdx.x;
-            pd[(int64_t)(2 * i) * G.pstride] = pr;
-            pd[(int64_t)(2 * i + 1) * G.pstride] = pi;
-        }
+        for (int q = 1; q < NS; ++q) rhs = n == q ? sys[q] : rhs;
+        pd_of(G, rhs, 0)[(int64_t)(2 * i + (k & 1)) * G.pstride + blockIdx.x] = dot[0];
     }
 }
 
-// Arnoldi step j, a correction pass: w -= sum_i h_i s_i v_i with h_i = s_i t_i and t the
-// totals of the partials of pass `src` (0: the operator kernel's <v_i, w>, 1: a second
-// pass's); then either the partials of <v_i, w> for a further pass (norm = 0) or of
-// |w|^2 (norm = 1). Workgroup 0 sets (src 0) or adds (src 1) h into column j of the
-// Hessenberg matrix.
-__global__ __launch_bounds__(MG_GWG) void mg_cgs_kernel(MgGmres G, int j, int src, int norm) {
-    __shared__ double h[2 * MG_IMAX];
-    __shared__ double lds[(MG_GWG / 64) * 2 * MG_IMAX];
+// Arnoldi step j: w -= sum_i h_i s_i v_i with h_i = s_i t_i and t the totals of the operator
+// kernel's <v_i, w>; then the partials of |w|^2. Workgroup 0 sets h in column j of the Hessenberg
+// matrix. JB > j bounds the basis vectors it loads. Bound by latency: every workgroup
+// re-sums all the partials. At the size above 8.8 us when every step loaded 24 basis vectors and
+// summed 48 totals by butterflies, 4.7, 5.6 and 6.4 us for JB = 8, 16, 24.
+template <int JB> __global__ __launch_bounds__(MG_GWG) void mg_cgs_kernel(MgGmres G, int j) {
+    __shared__ double h[2 * JB];
+    __shared__ double lds[MG_GWG / 64];
     const int rhs = G.active[blockIdx.y];
     const int K = G.K, tc = MG_GWG / K > 0 ? MG_GWG / K : 1;
     const int bl = threadIdx.x / K, a = threadIdx.x - bl * K;
     const int64_t b = (int64_t)blockIdx.x * tc + bl;
     const bool act = bl < tc && b < G.Nd;
-    const float2 *vb = G.basis + (int64_t)rhs * G.bstride;
-    float2 *w = const_cast<float2 *>(vb) + (int64_t)(j + 1) * G.vstride;
+    float2 *vb = G.basis + (int64_t)rhs * G.bstride;
+    float2 *w = vb + (int64_t)(j + 1) * G.vstride;
     // this thread's rows of w and of the basis, loaded before the partial sums
     // (unconditional loads with clamped indices: for i > j or a missing row they read a
     // stored row that enters with a zero coefficient or is not kept)
     const int64_t row = act ? b * K + a : 0;
     const float2 w0 = w[row];
-    float2 vi[MG_IMAX];
+    float2 vi[JB];
 #pragma unroll
-    for (int i = 0; i < MG_IMAX; ++i) vi[i] = vb[(int64_t)(i <= j ? i : j) * G.vstride + row];
-    // s_i in lane i of every wave (s_0 .. s_j are written; lanes past j read s_j)
+    for (int i = 0; i < JB; ++i) vi[i] = vb[(int64_t)(i <= j ? i : j) * G.vstride + row];
     const double *sc = G.sc + (int64_t)rhs * (MG_IMAX + 1);
-    const int lane = threadIdx.x & 63;
-    const double s_lane = sc[lane <= j ? lane : j];
-    load_totals<MG_GWG / 64>(pd_of(G, rhs, src), G.pstride, src == 0 ? G.nwa : G.nwc, 2 * (j + 1), h);
-    if (blockIdx.x == 0 && (int)threadIdx.x < 2 * (j + 1)) {
-        double *Hc = G.H + (int64_t)rhs * (MG_IMAX + 1) * MG_IMAX * 2 + 2 * (int64_t)j * (MG_IMAX + 1);
-        Hc[threadIdx.x] = (src == 0 ? 0.0 : Hc[threadIdx.x]) + h[threadIdx.x] * __shfl(s_lane, threadIdx.x >> 1, 64);
-    }
+    double *Hc = G.H + (int64_t)rhs * (MG_IMAX + 1) * MG_IMAX * 2 + 2 * (int64_t)j * (MG_IMAX + 1);
+    // s_i of the total this lane is given (s_0 .. s_j are written; past them s_j)
+    const int ti = totals_value<MG_GWG / 64, 2 * JB>() >> 1;
+    const double si = sc[ti <= j ? ti : j];
+    load_totals<MG_GWG / 64, 2 * JB>(pd_of(G, rhs, 0), G.pstride, G.nwa, 2 * (j + 1), [&](int v, double t) {
+        h[v] = t * si * si;
+        if (blockIdx.x == 0 && v < 2 * (j + 1)) Hc[v] = t * si;
+    });
     double yr = w0.x, yi = w0.y;
 #pragma unroll
-    for (int i = 0; i < MG_IMAX; ++i) {  // the terms i > j are zeros
-        const double si = __shfl(s_lane, i, 64);
-        const double cr = i <= j ? h[2 * i] * si * si : 0.0, ci = i <= j ? h[2 * i + 1] * si * si : 0.0;
+    for (int i = 0; i < JB; ++i) {  // the terms i > j are zeros
+        const double cr = h[2 * i], ci = h[2 * i + 1];
         yr -= cr * vi[i].x - ci * vi[i].y;
         yi -= cr * vi[i].y + ci * vi[i].x;
     }
     if (act) w[b * K + a] = make_float2((float)yr, (float)yi);
     yr = act ? (double)(float)yr : 0.0;
     yi = act ? (double)(float)yi : 0.0;
-    if (!norm) {
-        double acc[2 * MG_IMAX];
-#pragma unroll
-        for (int i = 0; i < MG_IMAX; ++i) {
-            acc[2 * i] = acc[2 * i + 1] = 0.0;
-            if (i <= j && act) {
-                acc[2 * i] = (double)vi[i].x * yr + (double)vi[i].y * yi;
-                acc[2 * i + 1] = (double)vi[i].x * yi - (double)vi[i].y * yr;
-            }
-        }
-        wg_sum_store<2 * MG_IMAX>(acc, lds, 2 * (j + 1), pd_of(G, rhs, 1) + blockIdx.x, G.pstride);
-    } else {
-        double n[1] = {yr * yr + yi * yi};
-        wg_sum_store<1>(n, lds, 1, pn_of(G, rhs, j + 1) + blockIdx.x, 1);
-    }
+    double n[1] = {yr * yr + yi * yi};
+    wg_sum_store<1>(n, lds, 1, pn_of(G, rhs, j + 1) + blockIdx.x, 1);
 }
 
 // Arnoldi step j of a cycle in one launch (classical Gram-Schmidt, one pass). The basis
@@ -801,24 +878,8 @@ __global__ __launch_bounds__(MG_AWG) __attribute__((amdgpu_waves_per_eu(1, 2))) 
     const int jp = j > 0 ? j - 1 : 0;  // the previous step (clamped)
 
     // ---- loads
-    // entry e of the LDS block: (aggregate bl, neighbour block d, row c)
     const int e = threadIdx.x;
-    const int ebl = e / (9 * K), erem = e - ebl * 9 * K, ed = erem / K, ec = erem - ed * K;
-    const int64_t eb = (int64_t)blockIdx.x * ta + ebl;
-    const bool eact = e < NE && ebl < ta && eb < G.Nd;
-    int64_t erow = 0;
-    {  // neighbour ed of aggregate eb without indexing the grid by a per-thread direction
-        const int gg[4] = {G.grid[0], G.grid[1], G.grid[2], G.grid[3]};
-        int gc[4], hc[4];
-        block_coords(gg, eact ? eb : 0, gc);
-        const int mu = (ed - 1) >> 1;
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            const int up = gc[m] + 1 == gg[m] ? 0 : gc[m] + 1, dn = gc[m] == 0 ? gg[m] - 1 : gc[m] - 1;
-            hc[m] = ed > 0 && m == mu ? ((ed & 1) ? up : dn) : gc[m];
-        }
-        erow = eact ? block_index(gg, hc) * K + ec : 0;
-    }
+    const int64_t erow = e < NE ? coarse_entry_row(G, e) : 0;
     const float2 ue = j > 0 ? uj[erow] : vb[erow];  // j = 0: v_0 itself
     float2 ve[JB];                                    // v_i at the entry, i < j
 #pragma unroll
@@ -850,7 +911,8 @@ __global__ __launch_bounds__(MG_AWG) __attribute__((amdgpu_waves_per_eu(1, 2))) 
     for (int q = 0; q < 4; ++q) pnr[q] = pnp[lane + 64 * q < G.nwa ? lane + 64 * q : 0];
     double np = 0;
     if (j > 0) {
-        load_totals<NW, 2 * JB>(pd_of(G, rhs, jp & 1), G.pstride, G.nwa, 2 * j, h);  // ends with a barrier
+        load_totals<NW, 2 * JB>(pd_of(G, rhs, jp & 1), G.pstride, G.nwa, 2 * j,
+                                [&](int v, double t) { h[v] = t; });  // ends with a barrier
 #pragma unroll
         for (int q = 0; q < 4; ++q) np += pnr[q] * (lane + 64 * q < G.nwa ? 1.0 : 0.0);
         for (int q = lane + 4 * 64; q < G.nwa; q += 64) np += pnp[q];
@@ -995,8 +1057,8 @@ __global__ __launch_bounds__(64) void mg_cfinal_kernel(MgGmres G, int k) {
         if (i < k) {
             // rotation [[c, s], [-conj(s), c]] with c a + s b = r, -conj(s) a + c b = 0 for
             // (a, b) = rows i, i + 1 of column i
-            const double ar = __shfl(hr[i], i, 64), ai = __shfl(hi[i], i, 64);
-            const double br = __shfl(hr[i + 1], i, 64), bi = __shfl(hi[i + 1], i, 64);
+            const double ar = lane_value(hr[i], i), ai = lane_value(hi[i], i);
+            const double br = lane_value(hr[i + 1], i), bi = lane_value(hi[i + 1], i);
             const double na = sqrt(ar * ar + ai * ai), nb = sqrt(br * br + bi * bi);
             double c, sr, si;
             if (nb == 0.0) {
@@ -1031,18 +1093,14 @@ __global__ __launch_bounds__(64) void mg_cfinal_kernel(MgGmres G, int k) {
 #pragma unroll
     for (int i = MG_IMAX - 1; i >= 0; --i) {
         if (i < k) {
-            double pr = 0.0, pi = 0.0;
+            double p[2] = {0.0, 0.0};
             if (lane > i && lane < k) {
-                pr = hr[i] * ylr - hi[i] * yli;
-                pi = hr[i] * yli + hi[i] * ylr;
+                p[0] = hr[i] * ylr - hi[i] * yli;
+                p[1] = hr[i] * yli + hi[i] * ylr;
             }
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) {
-                pr += __shfl_xor(pr, off, 64);
-                pi += __shfl_xor(pi, off, 64);
-            }
-            const double dr = __shfl(hr[i], i, 64), di = __shfl(hi[i], i, 64), dd = dr * dr + di * di;
-            const double tr = gr[i] - pr, ti = gi[i] - pi;
+            wave_scatter<2>(p);
+            const double dr = lane_value(hr[i], i), di = lane_value(hi[i], i), dd = dr * dr + di * di;
+            const double tr = gr[i] - lane_value(p[0], 0), ti = gi[i] - lane_value(p[0], 32);
             const double idd = dd > 0 ? 1.0 / dd : 0.0;
             if (lane == i) {
                 ylr = (tr * dr + ti * di) * idd;
@@ -1115,6 +1173,16 @@ static void launch_arnoldi(bool tail, int j, dim3 ga, hipStream_t st, const MgGm
     }
 }
 
+// Step j of the operator kernel. Four systems share a workgroup's stencil entries, so that one
+// pass over the stencil serves them.
+static void launch_capply(const MgGmres &G, int nact, int j, hipStream_t st) {
+    const int ns = nact >= 3 ? 4 : nact;
+    const dim3 g((unsigned)G.nwa, (unsigned)((nact + ns - 1) / ns));
+    if (ns == 1) hipLaunchKernelGGL(mg_capply_kernel<1>, g, dim3(MG_AWG), 0, st, G, j, nact);
+    else if (ns == 2) hipLaunchKernelGGL(mg_capply_kernel<2>, g, dim3(MG_AWG), 0, st, G, j, nact);
+    else hipLaunchKernelGGL(mg_capply_kernel<4>, g, dim3(MG_AWG), 0, st, G, j, nact);
+}
+
 hipError_t launch_mg_coarse_gmres(const MgGmres &G, int nact, int k, int cycles, hipStream_t st) {
     if (nact <= 0) return hipSuccess;
     if (k < 1 || k > MG_IMAX || cycles < 1 || G.K < 2 || G.K > 2 * MG_NVEC_MAX) return hipErrorInvalidValue;
@@ -1128,8 +1196,10 @@ hipError_t launch_mg_coarse_gmres(const MgGmres &G, int nact, int k, int cycles,
         } else {  // two launches per step
             hipLaunchKernelGGL(mg_cinit_kernel, gc, dim3(MG_GWG), 0, st, G);
             for (int j = 0; j < k; ++j) {
-                hipLaunchKernelGGL(mg_capply_kernel, ga, dim3(MG_AWG), 0, st, G, j);
-                hipLaunchKernelGGL(mg_cgs_kernel, gc, dim3(MG_GWG), 0, st, G, j, 0, 1);
+                launch_capply(G, nact, j, st);
+                if (j < 8) hipLaunchKernelGGL(mg_cgs_kernel<8>, gc, dim3(MG_GWG), 0, st, G, j);
+                else if (j < 16) hipLaunchKernelGGL(mg_cgs_kernel<16>, gc, dim3(MG_GWG), 0, st, G, j);
+                else hipLaunchKernelGGL(mg_cgs_kernel<MG_IMAX>, gc, dim3(MG_GWG), 0, st, G, j);
             }
         }
         hipLaunchKernelGGL(mg_cfinal_kernel, dim3((unsigned)nact), dim3(64), 0, st, G, k);
