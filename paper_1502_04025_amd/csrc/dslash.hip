@@ -1,8 +1,8 @@
 // dslash.hip - the Wilson-clover operator M on the whole lattice and its block-diagonal
 // part M_B (the domain-internal operator of the Schwarz splitting, Sec. 3.1).
 //
-// Full operator: one thread per (site, right-hand side); neighbours are read straight
-// from global memory. Workgroups are numbered so that the chunks of one block and right-hand
+// Full operator: one thread per (site, right-hand side); neighbours come from the workgroup's
+// tile in LDS (SpinorTile) or from global memory. Workgroups are numbered so that the chunks of one block and right-hand
 // side, then the block's right-hand sides, follow each other on the same XCD (workgroup w
 // runs on XCD w mod 8): neighbour spinors, links and clover are then re-read from that XCD's
 // L2 rather than through the fabric. Blocks are dealt to the XCDs one by one or, for few
@@ -54,9 +54,9 @@ template <class BK> __device__ __forceinline__ int canon_slot_of(const int (&x)[
     return x[0] % BK::bx + BK::bx * (x[1] % BK::by + BK::by * (x[2] % BK::bz + BK::bz * (x[3] % BK::bt)));
 }
 
-// Chunks of DSLASH_WG sites that make up one block (its even half, then its odd half):
-// they run next to each other on one XCD, so the hops between the two halves, most of a
-// site's neighbours, find the other half in that XCD's L2.
+// Chunks of DSLASH_WG sites that make up one block (with a tile the earlier, then the later half
+// of its time slices, else its even, then its odd half): they run next to each other on one
+// XCD, so the hops between them are read from that XCD's L2.
 template <class BK> constexpr int full_chunks_per_block() {
     return 2 * BK::Vbh > DSLASH_WG ? 2 * BK::Vbh / DSLASH_WG : 1;
 }
@@ -65,14 +65,66 @@ template <class BK> constexpr int full_chunks_per_block() {
 // the same XCD at about the same time and the face spinors come from its L2, as long as few
 // right-hand sides lie between them; with many, a block's own right-hand sides fill the L2
 // and dealing the blocks out one by one keeps the fabric's traffic even. FP64 operator in
-// us, one by one (block halves apart, as before) / one by one / ranges:
-//   16^3 x 32, 8x4^3, 1 rhs     72.3 / 72.7 / 53.9
-//   24^3 x 48, 4^4, 5 rhs       1116 / 1116 / 959
-//   48^3 x 96, 8x4^3, 2 rhs     8155 / 8152 / 6608
-//   32^3 x 64, 8x4^3, 6 rhs     3622 / 3752 / 3511
-//   32^3 x 64, 8x4^3, 12 rhs    6987 / 6865 / 6812   (FP32 input, with a residual: 17298 / 16650 / 17375)
-//   32^3 x 64, 4^4, 12 rhs      6611 / 6469 / 7186   (17087 / 16724 / 18202)
-static bool dslash_xcd_ranges(int nact) { return nact <= 8; }
+// us, one by one / ranges:
+//   16^3 x 32, 8x4^3, 1 rhs     56.0 / 46.9     4 rhs   123 / 118    8 rhs   234 / 231
+//   24^3 x 48, 4^4, 2 rhs        393 / 355      5 rhs   775 / 766
+//   32^3 x 64, 8x4^3, 1 rhs      848 / 746      6 rhs  2720 / 2845   12 rhs  5290 / 5400
+//   48^3 x 96, 8x4^3, 1 rhs     4250 / 3950     2 rhs  5485 / 5445
+//   32^3 x 64, 4^4, 2 rhs       1120 / 1093     12 rhs 5180 / 5401
+static bool dslash_xcd_ranges(int nact) { return nact <= 4; }
+
+// On 4^4 and 8x4^3 blocks a workgroup's 256 sites (both parities of a block, or of two of its
+// time slices) put their spinors into LDS, in storage precision: each is used there nine
+// times, and only the hops out of the tile, a quarter of them, read memory. Read straight
+// from global memory they keep the L1 busy (216 reads of 16 bytes a site in FP64); a third
+// wave per SIMD gained nothing. Operator alone, global / tile, in us:
+//   16^3 x 32, 8x4^3, 1 rhs      FP64 52.2 / 47.2, FP32 25.3 / 24.7
+//   24^3 x 48, 4^4, 5 rhs        FP64 966 / 772, FP32 545 / 448
+//   32^3 x 64, 8x4^3, 6 rhs      FP64 3640 / 2810, FP32 2150 / 1600
+//   32^3 x 64, 4^4, 12 rhs       FP64 6450 / 5170, FP32 3840 / 3150
+//   48^3 x 96, 8x4^3, 2 rhs      FP64 6770 / 5500, FP32 3690 / 2990
+// On 2^4 blocks half of all hops leave the block: they keep the reads from global memory. So
+// do FP16 spinors, which would gain as much, because the compiler fuses their site scale into
+// the projection in another order behind the tile's branches, and the rounding to FP16
+// storage would then give other results than before.
+template <class BK, class TI> struct SpinorTile {
+    static constexpr bool ON = BK::Vbh % (DSLASH_WG / 2) == 0 && !Storage<TI>::scaled;
+    static constexpr int W = Vec<TI>::W, NV = 24 / W, H = DSLASH_WG / 2;
+    static constexpr int BYTES = ON ? DSLASH_WG * NV * 16 : 0;
+    typedef typename Vec<TI>::type VT;
+    VT *lds;
+    __device__ __forceinline__ static VT load(const TI *d, int64_t bp, int q, int s) {
+        return ld_vec<false>(reinterpret_cast<const VT *>(d) + vec_index<TI, 24>(bp, q, s, BK::Vbh));
+    }
+    __device__ __forceinline__ void stage(const TI *d, int64_t bp, int s) const {
+#pragma unroll
+        for (int q = 0; q < NV; ++q) lds[q * DSLASH_WG + threadIdx.x] = load(d, bp, q, s);
+    }
+    // The spinor in slot n of the tile, or of site (bp, s) if it lies outside.
+    template <class R>
+    __device__ __forceinline__ void get(bool inside, int n, const TI *d, int64_t bp, int s, R (&out)[24]) const {
+        VT x[NV];
+        asm volatile("" : "+v"(n) : : "memory");  // the read stays behind the previous hop
+        if (inside) {
+#pragma unroll
+            for (int q = 0; q < NV; ++q) x[q] = lds[q * DSLASH_WG + n];
+        } else {
+#pragma unroll
+            for (int q = 0; q < NV; ++q) x[q] = load(d, bp, q, s);
+        }
+#pragma unroll
+        for (int q = 0; q < NV; ++q)
+#pragma unroll
+            for (int w = 0; w < W; ++w) out[q * W + w] = (R)x[q][w];
+    }
+};
+
+// Keeps a hop's arithmetic where it is written: the compiler otherwise moves that of all eight
+// hops behind the last of the tile's branches, and spills their spinors and links.
+template <class R> __device__ __forceinline__ void pin(R (&v)[24]) {
+#pragma unroll
+    for (int k = 0; k < 24; ++k) asm volatile("" : "+v"(v[k]));
+}
 
 template <class BK, class S, class TI, class TO, class R, bool CANON>
 __global__ __launch_bounds__(DSLASH_WG) void dslash_full_kernel(Geom geo, CF<S> links, CF<S> tclov, R kappa,
@@ -93,18 +145,43 @@ __global__ __launch_bounds__(DSLASH_WG) void dslash_full_kernel(Geom geo, CF<S> 
     const int rhs = active ? active[slot] : slot;
     const int64_t site = (int64_t)chunk * DSLASH_WG + threadIdx.x;
     const bool valid = chunk < nchunk && site < geo.V;
-    __shared__ CanonSlot<TO> lds[CANON ? DSLASH_WG : 1];
+    typedef SpinorTile<BK, TI> ST;
+    constexpr int CB = CANON ? DSLASH_WG * (int)sizeof(CanonSlot<TO>) : 16;
+    __shared__ __align__(16) char smem[ST::BYTES > CB ? ST::BYTES : CB];
+    CanonSlot<TO> *lds = reinterpret_cast<CanonSlot<TO> *>(smem);
+    const ST tile{reinterpret_cast<typename ST::VT *>(smem)};
     double nrm = 0.0;
+    // the workgroup's sites: with a tile, sites s0 .. s0 + 127 of both parities of a block
+    int64_t bp;
+    int s, s0 = 0;
+    if constexpr (ST::ON) {
+        s0 = chunk % G * ST::H;
+        bp = 2 * (int64_t)(chunk / G) + threadIdx.x / ST::H;
+        s = s0 + threadIdx.x % ST::H;
+    } else {
+        bp = site / Vbh;
+        s = (int)(site - bp * Vbh);
+    }
+    const TI *ind = in.data + (int64_t)rhs * ins_ * geo.V * 24;
+    const float *ins = in.scale ? in.scale + (int64_t)rhs * ins_ * geo.V : nullptr;
+    if constexpr (ST::ON) {  // a chunk is whole or past the lattice
+        if (valid) tile.stage(ind, bp, s);
+        __syncthreads();
+    }
+    int x[4] = {0, 0, 0, 0};
     if (valid) {
-        const int64_t bp = site / Vbh;
-        const int s = (int)(site - bp * Vbh);
-        int x[4];
         GeoC<BK>::coords(geo, bp, s, x);
         if (kap) kappa = (R)kap[rhs];
-        const int64_t ioff = (int64_t)rhs * ins_ * geo.V * 24;
         const int64_t ooff = (int64_t)rhs * outs_ * geo.V * 24;
-        const TI *ind = in.data + ioff;
-        const float *ins = in.scale ? in.scale + (int64_t)rhs * ins_ * geo.V : nullptr;
+        // the spinor of site (nbp, ns)
+        auto spinor = [&](int64_t nbp, int ns, R (&chi)[24]) {
+            if constexpr (ST::ON) {
+                const bool inside = (nbp >> 1) == (bp >> 1) && (unsigned)(ns - s0) < (unsigned)ST::H;
+                tile.get(inside, (int)(nbp & 1) * ST::H + ns - s0, ind, nbp, ns, chi);
+            } else {
+                load_site<R, 24>(ind, ins, nbp, ns, Vbh, chi);
+            }
+        };
         R acc[24];
 #pragma unroll
         for (int c = 0; c < 24; ++c) acc[c] = 0;
@@ -122,11 +199,12 @@ __global__ __launch_bounds__(DSLASH_WG) void dslash_full_kernel(Geom geo, CF<S> 
                 int ns;
                 GeoC<BK>::site(geo, y, nbp, ns);
                 R chi[24], h[12], u[18], uh[12];
-                load_site<R, 24>(ind, ins, nbp, ns, Vbh, chi);
+                spinor(nbp, ns, chi);
                 project<MU, -1>(chi, h);
                 load_reals<R, 72, 18 * MU, 18, S, true>(links.data, nullptr, bp, s, Vbh, u);
                 su3_mul(u, h, uh);
                 accum_recon<MU, -1>(acc, uh, sg * site_scale<R, S>(links.scale, bp, s, Vbh));
+                if constexpr (ST::ON) pin(acc);
             }
             {  // backward hop: (1 + gamma) U_mu(x - mu)^+ psi(x - mu)
                 int y[4] = {x[0], x[1], x[2], x[3]};
@@ -139,15 +217,16 @@ __global__ __launch_bounds__(DSLASH_WG) void dslash_full_kernel(Geom geo, CF<S> 
                 int ns;
                 GeoC<BK>::site(geo, y, nbp, ns);
                 R chi[24], h[12], u[18], uh[12];
-                load_site<R, 24>(ind, ins, nbp, ns, Vbh, chi);
+                spinor(nbp, ns, chi);
                 project<MU, +1>(chi, h);
                 load_reals<R, 72, 18 * MU, 18, S, true>(links.data, nullptr, nbp, ns, Vbh, u);
                 su3_dag_mul(u, h, uh);
                 accum_recon<MU, +1>(acc, uh, sg * site_scale<R, S>(links.scale, nbp, ns, Vbh));
+                if constexpr (ST::ON) pin(acc);
             }
         });
         R psi[24], res[24];
-        load_site<R, 24>(ind, ins, bp, s, Vbh, psi);
+        spinor(bp, s, psi);
         CloverRegs<S, R> cl;
         cl.load(tclov.data, tclov.scale, bp, s, Vbh);
         clover_mul(cl, psi, res, kappa);  // (1 + kappa T) psi
@@ -164,9 +243,12 @@ __global__ __launch_bounds__(DSLASH_WG) void dslash_full_kernel(Geom geo, CF<S> 
             // of its own the calls are 2 to 15% faster (32^3 x 64, 8x4^3, 4 rhs, FP64
             // 3568 -> 3079 us, FP32 2078 -> 1903 us, FP16 1524 -> 1493 us; 16^3 x 32, 1 rhs, FP64
             // 80.7 -> 73.5 us).
-            // Slots in canonical order where the chunk holds both parities of its blocks
-            const int n = 2 * Vbh <= DSLASH_WG ? canon_slot_of<BK>(x) + (int)(bp / 2 % (DSLASH_WG / (2 * Vbh))) * 2 * Vbh
-                                               : (int)threadIdx.x;
+            // slots in canonical order where the chunk holds both parities of its blocks
+            int n = threadIdx.x;
+            if constexpr (ST::ON) n = canon_slot_of<BK>(x) - 2 * s0;
+            else if constexpr (2 * Vbh <= DSLASH_WG)
+                n = canon_slot_of<BK>(x) + (int)(bp / 2 % (DSLASH_WG / (2 * Vbh))) * 2 * Vbh;
+            if constexpr (ST::ON) __syncthreads();  // the tile has been read
             lds[n].set(res);
             lds[n].idx = x[0] + (int64_t)geo.L[0] * (x[1] + (int64_t)geo.L[1] * (x[2] + (int64_t)geo.L[2] * x[3]));
         } else {
