@@ -756,6 +756,15 @@ static int apply_common(sapdd_ctx *c, const sapdd_field *fc, double kappa, int p
         CHK(buf(c, "stage_out", nd * 8, &d));
         dst = (double *)d;
     }
+    // The block operators read and write the caller's arrays: one workgroup the sites of one
+    // block and right-hand side, so both may be the same array, but an input that overlaps
+    // the output in another way is copied first.
+    if (block && src != dst && src < dst + nd && dst < src + nd) {
+        void *d;
+        CHK(buf(c, "stage_in", nd * 8, &d));
+        HIPCHK(c, launch_copy(src, d, (int64_t)nd * 8, c->stream));
+        src = (const double *)d;
+    }
     if (two_row) {
         KLAUNCH(c, SAPDD_K_BLOCK_DSLASH,
                 launch_dslash_block12(g, f->links12[prec], tclov_of(f, prec), kappa, src, dst, nrhs, c->stream));

@@ -27,3 +27,19 @@ def test_operator_alone_and_in_a_batch(ctx, dims, block, prec):  # noqa: F811
         np.testing.assert_array_equal(f.apply_D(0.124, psi[r:r + 1], prec=prec)[0], out[r])
     for r in (1, 5):
         assert relerr(out[r], wilson.apply_M(u, t, 0.124, psi[r])) <= TOL[prec]
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+def test_operators_on_overlapping_arrays(ctx, shift):  # noqa: F811
+    """The output may be the input, or overlap it by some of its right-hand sides."""
+    import torch
+    dims, block = (8, 8, 8, 8), (4, 4, 4, 4)
+    _, _, f = setup_case(ctx, dims, block)
+    psi = torch.from_numpy(synthetic.gaussian_source(dims, 9, 12)).cuda()
+    torch.cuda.synchronize()
+    for call in (f.apply_D, f.apply_block_D, lambda *a, **k: f.apply_block_D(*a, links12=True, **k)):
+        ref = call(0.124, psi[:8].clone(), prec="f32")
+        x = psi.clone()
+        torch.cuda.synchronize()
+        call(0.124, x[:8], prec="f32", out=x[shift:8 + shift])
+        assert torch.equal(x[shift:8 + shift], ref)
