@@ -759,7 +759,8 @@ static int apply_common(sapdd_ctx *c, const sapdd_field *fc, double kappa, int p
     // The block operators read and write the caller's arrays: one workgroup the sites of one
     // block and right-hand side, so both may be the same array, but an input that overlaps
     // the output in another way is copied first.
-    if (block && src != dst && src < dst + nd && dst < src + nd) {
+    const bool overlap = src < dst + nd && dst < src + nd;
+    if (block && src != dst && overlap) {
         void *d;
         CHK(buf(c, "stage_in", nd * 8, &d));
         HIPCHK(c, launch_copy(src, d, (int64_t)nd * 8, c->stream));
@@ -771,11 +772,14 @@ static int apply_common(sapdd_ctx *c, const sapdd_field *fc, double kappa, int p
     } else if (block) {
         KLAUNCH(c, SAPDD_K_BLOCK_DSLASH, launch_dslash_block(g, links_of(f, prec), tclov_of(f, prec), kappa, src, dst, nrhs, c->stream));
     } else {
-        Fld fin;
-        CHK(spinor_buf(c, "op_in", g, nrhs, prec, 24, &fin));
-        HIPCHK(c, launch_pack(g, 24, nrhs, src, fin, c->stream));
         DslashIO io{};
-        io.in = fin;
+        io.canon_in = dslash_reads_canon(g, prec) && !overlap;
+        if (io.canon_in) {
+            io.in = Fld{const_cast<double *>(src), nullptr, prec};
+        } else {
+            CHK(spinor_buf(c, "op_in", g, nrhs, prec, 24, &io.in));
+            HIPCHK(c, launch_pack(g, 24, nrhs, src, io.in, c->stream));
+        }
         io.canon = dst;
         io.nact = nrhs;
         io.in_stride = 1;

@@ -87,10 +87,11 @@ static bool dslash_xcd_ranges(int nact) { return nact <= 4; }
 // do FP16 spinors, which would gain as much, because the compiler fuses their site scale into
 // the projection in another order behind the tile's branches, and the rounding to FP16
 // storage would then give other results than before.
-template <class BK, class TI> struct SpinorTile {
+template <class BK, class TI, bool CIN> struct SpinorTile {
     static constexpr bool ON = BK::Vbh % (DSLASH_WG / 2) == 0 && !Storage<TI>::scaled;
     static constexpr int W = Vec<TI>::W, NV = 24 / W, H = DSLASH_WG / 2;
-    static constexpr int BYTES = ON ? DSLASH_WG * NV * 16 : 0;
+    static constexpr int PITCH = CIN ? DSLASH_WG + 1 : DSLASH_WG;  // neighbouring lanes write a site's vectors
+    static constexpr int BYTES = ON ? PITCH * NV * 16 : 0;
     typedef typename Vec<TI>::type VT;
     VT *lds;
     __device__ __forceinline__ static VT load(const TI *d, int64_t bp, int q, int s) {
@@ -98,19 +99,55 @@ template <class BK, class TI> struct SpinorTile {
     }
     __device__ __forceinline__ void stage(const TI *d, int64_t bp, int s) const {
 #pragma unroll
-        for (int q = 0; q < NV; ++q) lds[q * DSLASH_WG + threadIdx.x] = load(d, bp, q, s);
+        for (int q = 0; q < NV; ++q) lds[q * PITCH + threadIdx.x] = load(d, bp, q, s);
     }
-    // The spinor in slot n of the tile, or of site (bp, s) if it lies outside.
+    // The tile of block b from sites s0 on of both parities, from the operator API's canonical
+    // array: whole rows in x by neighbouring lanes, rounded to storage precision as a pass of
+    // its own would. That pass moves every spinor once more; without it a call takes, in us,
+    //   16^3 x 32, 1 rhs FP64 74 -> 57, FP32 45 -> 41    32^3 x 64, 6 rhs FP64 3524 -> 2705
+    //   32^3 x 64, 4^4, 1 rhs FP32 523 -> 479            24 x 8 x 40 x 56, 3 rhs FP32 253 -> 233
+    // FP16 sites need their maximum first, and 2^4 blocks have no tile: they keep the pass.
+    __device__ __forceinline__ void stage_canon(const Geom &geo, const double *d, int64_t b, int s0) const {
+        constexpr int ROW = 12 * BK::bx;
+        const int B[4] = {BK::bx, BK::by, BK::bz, BK::bt};
+        int g[4];
+        block_coords(geo.G, b, g);
+        const int t0 = 2 * s0 / (BK::bx * BK::by * BK::bz);
+#pragma unroll
+        for (int i = 0; i < 12; ++i) {
+            const int j = i * DSLASH_WG + threadIdx.x, row = j / ROW, q = j % 12;
+            const int l[4] = {j % ROW / 12, row % BK::by, row / BK::by % BK::bz, row / (BK::by * BK::bz) + t0};
+            const int64_t idx = g[0] * BK::bx + l[0] +
+                                (int64_t)geo.L[0] * (g[1] * BK::by + l[1] +
+                                                     (int64_t)geo.L[1] * (g[2] * BK::bz + l[2] + (int64_t)geo.L[2] * (g[3] * BK::bt + l[3])));
+            const dv2g x = ((const SAPDD_GLOBAL dv2g *)d)[idx * 12 + q];
+            const int n = ((l[0] + l[1] + l[2] + l[3]) & 1) * H + local_half_index(B, l) - s0;
+            TI *to = (TI *)(lds + 2 * q / W * PITCH + n) + 2 * q % W;
+            to[0] = (TI)x.x, to[1] = (TI)x.y;
+        }
+    }
+    // The spinor in slot n of the tile, or of site (bp, s), canonical index idx, if it lies outside.
     template <class R>
-    __device__ __forceinline__ void get(bool inside, int n, const TI *d, int64_t bp, int s, R (&out)[24]) const {
+    __device__ __forceinline__ void get(bool inside, int n, const TI *d, int64_t bp, int s, const double *canon,
+                                        int64_t idx, R (&out)[24]) const {
         VT x[NV];
         asm volatile("" : "+v"(n) : : "memory");  // the read stays behind the previous hop
         if (inside) {
 #pragma unroll
-            for (int q = 0; q < NV; ++q) x[q] = lds[q * DSLASH_WG + n];
+            for (int q = 0; q < NV; ++q) x[q] = lds[q * PITCH + n];
         } else {
 #pragma unroll
-            for (int q = 0; q < NV; ++q) x[q] = load(d, bp, q, s);
+            for (int q = 0; q < NV; ++q) {
+                if constexpr (CIN) {
+#pragma unroll
+                    for (int k = 0; k < W; k += 2) {
+                        const dv2g e = ((const SAPDD_GLOBAL dv2g *)canon)[idx * 12 + (q * W + k) / 2];
+                        x[q][k] = (TI)e.x, x[q][k + 1] = (TI)e.y;
+                    }
+                } else {
+                    x[q] = load(d, bp, q, s);
+                }
+            }
         }
 #pragma unroll
         for (int q = 0; q < NV; ++q)
@@ -126,7 +163,7 @@ template <class R> __device__ __forceinline__ void pin(R (&v)[24]) {
     for (int k = 0; k < 24; ++k) asm volatile("" : "+v"(v[k]));
 }
 
-template <class BK, class S, class TI, class TO, class R, bool CANON>
+template <class BK, class S, class TI, class TO, class R, bool CANON, bool CIN = false>
 __global__ __launch_bounds__(DSLASH_WG) void dslash_full_kernel(Geom geo, CF<S> links, CF<S> tclov, R kappa,
                                                                  CF<TI> in, MF<TO> out, double *canon,
                                                                  const double *sub,
@@ -145,7 +182,7 @@ __global__ __launch_bounds__(DSLASH_WG) void dslash_full_kernel(Geom geo, CF<S> 
     const int rhs = active ? active[slot] : slot;
     const int64_t site = (int64_t)chunk * DSLASH_WG + threadIdx.x;
     const bool valid = chunk < nchunk && site < geo.V;
-    typedef SpinorTile<BK, TI> ST;
+    typedef SpinorTile<BK, TI, CIN> ST;
     constexpr int CB = CANON ? DSLASH_WG * (int)sizeof(CanonSlot<TO>) : 16;
     __shared__ __align__(16) char smem[ST::BYTES > CB ? ST::BYTES : CB];
     CanonSlot<TO> *lds = reinterpret_cast<CanonSlot<TO> *>(smem);
@@ -163,9 +200,13 @@ __global__ __launch_bounds__(DSLASH_WG) void dslash_full_kernel(Geom geo, CF<S> 
         s = (int)(site - bp * Vbh);
     }
     const TI *ind = in.data + (int64_t)rhs * ins_ * geo.V * 24;
+    const double *cin = CIN ? (const double *)in.data + (int64_t)rhs * geo.V * 24 : nullptr;
     const float *ins = in.scale ? in.scale + (int64_t)rhs * ins_ * geo.V : nullptr;
     if constexpr (ST::ON) {  // a chunk is whole or past the lattice
-        if (valid) tile.stage(ind, bp, s);
+        if (valid) {
+            if constexpr (CIN) tile.stage_canon(geo, cin, bp >> 1, s0);
+            else tile.stage(ind, bp, s);
+        }
         __syncthreads();
     }
     int x[4] = {0, 0, 0, 0};
@@ -174,10 +215,11 @@ __global__ __launch_bounds__(DSLASH_WG) void dslash_full_kernel(Geom geo, CF<S> 
         if (kap) kappa = (R)kap[rhs];
         const int64_t ooff = (int64_t)rhs * outs_ * geo.V * 24;
         // the spinor of site (nbp, ns)
-        auto spinor = [&](int64_t nbp, int ns, R (&chi)[24]) {
+        auto spinor = [&](int64_t nbp, int ns, const int (&y)[4], R (&chi)[24]) {
             if constexpr (ST::ON) {
                 const bool inside = (nbp >> 1) == (bp >> 1) && (unsigned)(ns - s0) < (unsigned)ST::H;
-                tile.get(inside, (int)(nbp & 1) * ST::H + ns - s0, ind, nbp, ns, chi);
+                tile.get(inside, (int)(nbp & 1) * ST::H + ns - s0, ind, nbp, ns, cin,
+                         y[0] + (int64_t)geo.L[0] * (y[1] + (int64_t)geo.L[1] * (y[2] + (int64_t)geo.L[2] * y[3])), chi);
             } else {
                 load_site<R, 24>(ind, ins, nbp, ns, Vbh, chi);
             }
@@ -199,7 +241,7 @@ __global__ __launch_bounds__(DSLASH_WG) void dslash_full_kernel(Geom geo, CF<S> 
                 int ns;
                 GeoC<BK>::site(geo, y, nbp, ns);
                 R chi[24], h[12], u[18], uh[12];
-                spinor(nbp, ns, chi);
+                spinor(nbp, ns, y, chi);
                 project<MU, -1>(chi, h);
                 load_reals<R, 72, 18 * MU, 18, S, true>(links.data, nullptr, bp, s, Vbh, u);
                 su3_mul(u, h, uh);
@@ -217,7 +259,7 @@ __global__ __launch_bounds__(DSLASH_WG) void dslash_full_kernel(Geom geo, CF<S> 
                 int ns;
                 GeoC<BK>::site(geo, y, nbp, ns);
                 R chi[24], h[12], u[18], uh[12];
-                spinor(nbp, ns, chi);
+                spinor(nbp, ns, y, chi);
                 project<MU, +1>(chi, h);
                 load_reals<R, 72, 18 * MU, 18, S, true>(links.data, nullptr, nbp, ns, Vbh, u);
                 su3_dag_mul(u, h, uh);
@@ -226,7 +268,7 @@ __global__ __launch_bounds__(DSLASH_WG) void dslash_full_kernel(Geom geo, CF<S> 
             }
         });
         R psi[24], res[24];
-        spinor(bp, s, psi);
+        spinor(bp, s, x, psi);
         CloverRegs<S, R> cl;
         cl.load(tclov.data, tclov.scale, bp, s, Vbh);
         clover_mul(cl, psi, res, kappa);  // (1 + kappa T) psi
@@ -284,7 +326,7 @@ int dslash_full_partials(const Geom &geo) {
     return (nchunk + 7) / 8 * 8;
 }
 
-template <class BK, class S, class TI, class TO, class R, bool CANON>
+template <class BK, class S, class TI, class TO, class R, bool CANON, bool CIN = false>
 static hipError_t full_typed(const Geom &geo, Fld links, Fld tclov, double kappa, const DslashIO &io,
                              hipStream_t st) {
     const int nchunk = (int)((geo.V + DSLASH_WG - 1) / DSLASH_WG);
@@ -296,7 +338,7 @@ static hipError_t full_typed(const Geom &geo, Fld links, Fld tclov, double kappa
     if (nwg == 0) return hipSuccess;
     // the block grid is even in every direction: the lattice is whole chunks
     if (nwg > 0x7fffffff || geo.V % DSLASH_WG != 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((dslash_full_kernel<BK, S, TI, TO, R, CANON>), dim3((unsigned)nwg), dim3(DSLASH_WG), 0, st, geo,
+    hipLaunchKernelGGL((dslash_full_kernel<BK, S, TI, TO, R, CANON, CIN>), dim3((unsigned)nwg), dim3(DSLASH_WG), 0, st, geo,
                        CF<S>{(const S *)links.data, links.scale}, CF<S>{(const S *)tclov.data, tclov.scale},
                        (R)kappa, CF<TI>{(const TI *)io.in.data, io.in.scale}, MF<TO>{(TO *)io.out.data, io.out.scale},
                        io.canon, io.sub, io.part, io.active, io.nact, nchunk, dslash_xcd_ranges(io.nact) ? 1 : 0, io.in_stride, io.out_stride, io.sub_stride,
@@ -312,6 +354,13 @@ static hipError_t full_shape(const Geom &geo, Fld links, Fld tclov, double kappa
     // operator API).
     if (io.canon) {
         if (io.in.prec != links.prec || io.sub || io.part) return hipErrorInvalidValue;
+        if (io.canon_in) {
+            if constexpr (SpinorTile<BK, float, true>::ON) {
+                if (links.prec == P64) return full_typed<BK, double, double, double, double, true, true>(geo, links, tclov, kappa, io, st);
+                if (links.prec == P32) return full_typed<BK, float, float, float, float, true, true>(geo, links, tclov, kappa, io, st);
+            }
+            return hipErrorInvalidValue;
+        }
         if (links.prec == P64) return full_typed<BK, double, double, double, double, true>(geo, links, tclov, kappa, io, st);
         if (links.prec == P32) return full_typed<BK, float, float, float, float, true>(geo, links, tclov, kappa, io, st);
         return full_typed<BK, half_t, half_t, half_t, float, true>(geo, links, tclov, kappa, io, st);
@@ -336,6 +385,8 @@ template <class BK> struct FullRun {
         return full_shape<BK>(geo, links, tclov, kappa, io, st);
     }
 };
+
+bool dslash_reads_canon(const Geom &geo, int prec) { return prec != P16 && geo.Vbh % (DSLASH_WG / 2) == 0; }
 
 hipError_t launch_dslash_full(const Geom &geo, Fld links, Fld tclov, double kappa, const DslashIO &io,
                               hipStream_t st) {

@@ -41,6 +41,8 @@ hipError_t launch_sap_clover(const Geom &geo, const double *tclov, double kappa,
 struct DslashIO {
     Fld in;            // spinor of rhs r at in + r * in_stride * V * 24 (scales: * V)
     Fld out;           // idem with out_stride
+    bool canon_in;     // in.data is a canonical FP64 array, to be rounded to in.prec (with canon, where
+                       // dslash_reads_canon)
     double *canon;     // if set: the result goes to this canonical FP64 array instead (one
                        // array of V * 24 per slot), rounded to the links' precision
     const double *sub; // if set (FP64 out only): out = sub - M in, rhs stride sub_stride
@@ -52,6 +54,8 @@ struct DslashIO {
 };
 // Number of partial sums launch_dslash_full writes per RHS slot.
 int dslash_full_partials(const Geom &geo);
+// Whether the operator API's input at this precision may stay a canonical array.
+bool dslash_reads_canon(const Geom &geo, int prec);
 // out = M in over the whole lattice. links/clov in `lprec` (FP64: links + T in FP64).
 hipError_t launch_dslash_full(const Geom &geo, Fld links, Fld tclov, double kappa, const DslashIO &io,
                               hipStream_t st);

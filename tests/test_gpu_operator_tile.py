@@ -6,16 +6,32 @@ import pytest
 
 import synthetic
 from oracle import wilson
-from test_gpu_operator import TOL, ctx, relerr, setup_case  # noqa: F401
+from test_gpu_operator import TOL, ctx, relerr  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture
+def setup(ctx):  # noqa: F811
+    fields = []
+
+    def make(dims, block):
+        u = synthetic.gauge_field(dims, 0.3, 5)
+        f = ctx.load_gauge(u, block)
+        f.compute_clover(1.0)
+        fields.append(f)
+        return u, wilson.clover_term(u, 1.0), f
+
+    yield make
+    for f in fields:
+        f.free()
+
+
 @pytest.mark.parametrize("dims,block", [((8, 8, 16, 24), (4, 4, 4, 4)), ((32, 8, 8, 16), (8, 4, 4, 4))])
 @pytest.mark.parametrize("prec", ["f64", "f32", "f16"])
-def test_operator_alone_and_in_a_batch(ctx, dims, block, prec):  # noqa: F811
+def test_operator_alone_and_in_a_batch(setup, dims, block, prec):
     print(f"D tile {dims} {block} {prec}", flush=True)
-    u, t, f = setup_case(ctx, dims, block)
+    u, t, f = setup(dims, block)
     psi = synthetic.gaussian_source(dims, 6, 9)
     psi[1] = 0
     lx, ly, lz, lt = dims
@@ -30,11 +46,11 @@ def test_operator_alone_and_in_a_batch(ctx, dims, block, prec):  # noqa: F811
 
 
 @pytest.mark.parametrize("shift", [0, 1])
-def test_operators_on_overlapping_arrays(ctx, shift):  # noqa: F811
+def test_operators_on_overlapping_arrays(setup, shift):
     """The output may be the input, or overlap it by some of its right-hand sides."""
     import torch
     dims, block = (8, 8, 8, 8), (4, 4, 4, 4)
-    _, _, f = setup_case(ctx, dims, block)
+    _, _, f = setup(dims, block)
     psi = torch.from_numpy(synthetic.gaussian_source(dims, 9, 12)).cuda()
     torch.cuda.synchronize()
     for call in (f.apply_D, f.apply_block_D, lambda *a, **k: f.apply_block_D(*a, links12=True, **k)):
