@@ -247,6 +247,16 @@ template <class BK> __device__ __forceinline__ int64_t canon_index_bk(const Geom
            (int64_t)geo.L[0] * (g[1] * BK::by + l[1] +
                                 (int64_t)geo.L[1] * (g[2] * BK::bz + l[2] + (int64_t)geo.L[2] * (g[3] * BK::bt + l[3])));
 }
+// Block and right-hand side of workgroup w of Nd * nrhs (Nd a multiple of 8): workgroups run on XCD
+// w mod 8, and the right-hand sides of one block follow each other there, so that all but the
+// first read its links and clover from that XCD's L2. A call in us, all blocks of one
+// right-hand side first / this order: 24 x 8 x 40 x 56, 4^4, 3 rhs FP64 413 / 350, FP32 204 / 181;
+// 32^3 x 64, 8x4^3, 4 rhs FP64 3336 / 3179, FP32 1596 / 1317, FP16 1235 / 1160.
+__device__ __forceinline__ int64_t block_and_rhs(int nrhs, int &rhs) {
+    const int w = blockIdx.x, k = w >> 3;
+    rhs = k % nrhs;
+    return (int64_t)(k / nrhs) * 8 + (w & 7);
+}
 // The site at canonical index idx, in storage precision S.
 template <class S, class R> __device__ __forceinline__ void block_load(const double *in, int64_t idx, R (&psi)[24]) {
     double e[24];

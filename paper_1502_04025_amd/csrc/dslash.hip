@@ -400,24 +400,24 @@ hipError_t launch_dslash_full(const Geom &geo, Fld links, Fld tclov, double kapp
 // clover. 32^3 x 64, 4^4 blocks, one call with its conversions, against separate passes before
 // and after: FP32 545 -> 362 us, FP16 412 -> 270 us, FP64 949 -> 704 us; the kernel alone moves
 // 5.3 TB/s in FP32 and 5.1 TB/s in FP16.
-template <class BK, class S, class R>
+template <class BK, class S, class R, bool ONE>
 __global__ __launch_bounds__(BK::NT) void dslash_block_kernel(Geom geo, CF<S> links, CF<S> tclov, R kappa,
-                                                               const double *in, double *out) {
+                                                               const double *in, double *out, int nrhs) {
     constexpr int Vbh = BK::Vbh;
     // one area for the hops (one LDS buffer: this memory-bound kernel gains more from
     // occupancy than from the barrier a second buffer would save) and then for the result
     __shared__ __align__(16) char lds[BlockLds<BK, S, R>::bytes];
     const SiteInfo si = site_info<BK>(threadIdx.x);
-    const int64_t b = blockIdx.x;
-    const int rhs = blockIdx.y;
+    int rhs;
+    const int64_t b = block_and_rhs(ONE ? 1 : nrhs, rhs);
     const int64_t bp = 2 * b + si.p;
     const int64_t idx = canon_index_bk<BK>(geo, b, si.l);
     // links held in registers between the two half-hops (re-reading them from L1/L2 to
     // reach 4 waves per SIMD measured slower: 3.65 vs 4.53 TB/s in FP16)
-    // Every byte of links and clover is used by one workgroup only: non-temporal hints
-    // (measured 4.71 -> 5.52 TB/s in FP32, 4.49 -> 4.80 TB/s in FP16 on 32^3x64). Issuing
+    // With one right-hand side every byte of links and clover is used by one workgroup only:
+    // non-temporal hints (measured 4.71 -> 5.52 TB/s in FP32, 4.49 -> 4.80 TB/s in FP16 on 32^3x64). Issuing
     // the clover loads before the hops instead of after measured slower.
-    constexpr bool NT = true;
+    constexpr bool NT = ONE;
     SiteLinks<S, R> U;
     U.template init<NT>(links.data, links.scale, bp, si.s, Vbh);
     R psi[24], hop[24];
@@ -433,24 +433,25 @@ __global__ __launch_bounds__(BK::NT) void dslash_block_kernel(Geom geo, CF<S> li
     block_store<BK, S>(out + (int64_t)rhs * geo.V * 24, idx, si.l, res, lds);
 }
 
+template <class BK, class S, class R>
+static hipError_t block_typed(const Geom &geo, Fld links, Fld tclov, double kappa, const double *in, double *out,
+                              int nrhs, hipStream_t st) {
+    const int64_t nwg = geo.Nd * nrhs;
+    if (geo.Nd % 8 != 0 || nwg > 0x7fffffff) return hipErrorInvalidValue;
+    const CF<S> l{(const S *)links.data, links.scale}, t{(const S *)tclov.data, tclov.scale};
+    if (nrhs == 1)
+        hipLaunchKernelGGL((dslash_block_kernel<BK, S, R, true>), dim3((unsigned)nwg), dim3(BK::NT), 0, st, geo, l, t, (R)kappa, in, out, nrhs);
+    else
+        hipLaunchKernelGGL((dslash_block_kernel<BK, S, R, false>), dim3((unsigned)nwg), dim3(BK::NT), 0, st, geo, l, t, (R)kappa, in, out, nrhs);
+    return hipGetLastError();
+}
 template <class BK>
 static hipError_t block_shape(const Geom &geo, Fld links, Fld tclov, double kappa, const double *in, double *out,
                               int nrhs, hipStream_t st) {
     if (tclov.prec != links.prec) return hipErrorInvalidValue;
-    dim3 grid((unsigned)geo.Nd, (unsigned)nrhs);
-    if (links.prec == P64)
-        hipLaunchKernelGGL((dslash_block_kernel<BK, double, double>), grid, dim3(BK::NT), 0, st, geo,
-                           CF<double>{(const double *)links.data, nullptr}, CF<double>{(const double *)tclov.data, nullptr},
-                           kappa, in, out);
-    else if (links.prec == P32)
-        hipLaunchKernelGGL((dslash_block_kernel<BK, float, float>), grid, dim3(BK::NT), 0, st, geo,
-                           CF<float>{(const float *)links.data, nullptr}, CF<float>{(const float *)tclov.data, nullptr},
-                           (float)kappa, in, out);
-    else
-        hipLaunchKernelGGL((dslash_block_kernel<BK, half_t, float>), grid, dim3(BK::NT), 0, st, geo,
-                           CF<half_t>{(const half_t *)links.data, links.scale},
-                           CF<half_t>{(const half_t *)tclov.data, tclov.scale}, (float)kappa, in, out);
-    return hipGetLastError();
+    if (links.prec == P64) return block_typed<BK, double, double>(geo, links, tclov, kappa, in, out, nrhs, st);
+    if (links.prec == P32) return block_typed<BK, float, float>(geo, links, tclov, kappa, in, out, nrhs, st);
+    return block_typed<BK, half_t, float>(geo, links, tclov, kappa, in, out, nrhs, st);
 }
 
 template <class BK> struct BlockRun {

@@ -75,18 +75,18 @@ __global__ void links12_pack_kernel(Geom geo, const double *__restrict__ links, 
     store_site<float, 48, S>(out, scale, bp, s, geo.Vbh, v);
 }
 
-template <class BK, class S, class R>
+template <class BK, class S, class R, bool ONE>
 __global__ __launch_bounds__(BK::NT) void dslash_block12_kernel(Geom geo, const S *links12, const float *lscale,
                                                                 const S *tclov, const float *tscale, R kappa,
-                                                                const double *in, double *out) {
+                                                                const double *in, double *out, int nrhs) {
     constexpr int Vbh = BK::Vbh;
     __shared__ __align__(16) char lds[BlockLds<BK, S, R>::bytes];
     const SiteInfo si = site_info<BK>(threadIdx.x);
-    const int64_t b = blockIdx.x;
-    const int rhs = blockIdx.y;
+    int rhs;
+    const int64_t b = block_and_rhs(ONE ? 1 : nrhs, rhs);
     const int64_t bp = 2 * b + si.p;
     const int64_t idx = canon_index_bk<BK>(geo, b, si.l);
-    constexpr bool NT = true;  // every byte is used by one workgroup only
+    constexpr bool NT = ONE;  // every byte is used by one workgroup only
     SiteLinks12<S, R> U;
     U.template init<NT>(links12, lscale, bp, si.s, Vbh);
     R psi[24], hop[24];
@@ -102,21 +102,25 @@ __global__ __launch_bounds__(BK::NT) void dslash_block12_kernel(Geom geo, const 
     block_store<BK, S>(out + (int64_t)rhs * geo.V * 24, idx, si.l, res, lds);
 }
 
+template <class BK, class S, bool ONE>
+hipError_t block12_typed(const Geom &geo, Fld links12, Fld tclov, double kappa, const double *in, double *out,
+                         int nrhs, hipStream_t st) {
+    const int64_t nwg = geo.Nd * nrhs;
+    if (geo.Nd % 8 != 0 || nwg > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((dslash_block12_kernel<BK, S, float, ONE>), dim3((unsigned)nwg), dim3(BK::NT), 0, st, geo,
+                       (const S *)links12.data, links12.scale, (const S *)tclov.data, tclov.scale, (float)kappa, in,
+                       out, nrhs);
+    return hipGetLastError();
+}
 template <class BK>
 hipError_t block12_shape(const Geom &geo, Fld links12, Fld tclov, double kappa, const double *in, double *out,
                          int nrhs, hipStream_t st) {
-    if (tclov.prec != links12.prec) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)geo.Nd, (unsigned)nrhs);
+    if (tclov.prec != links12.prec || links12.prec == P64) return hipErrorInvalidValue;
     if (links12.prec == P32)
-        hipLaunchKernelGGL((dslash_block12_kernel<BK, float, float>), grid, dim3(BK::NT), 0, st, geo,
-                           (const float *)links12.data, nullptr, (const float *)tclov.data, nullptr, (float)kappa, in, out);
-    else if (links12.prec == P16)
-        hipLaunchKernelGGL((dslash_block12_kernel<BK, half_t, float>), grid, dim3(BK::NT), 0, st, geo,
-                           (const half_t *)links12.data, links12.scale, (const half_t *)tclov.data, tclov.scale,
-                           (float)kappa, in, out);
-    else
-        return hipErrorInvalidValue;
-    return hipGetLastError();
+        return nrhs == 1 ? block12_typed<BK, float, true>(geo, links12, tclov, kappa, in, out, nrhs, st)
+                         : block12_typed<BK, float, false>(geo, links12, tclov, kappa, in, out, nrhs, st);
+    return nrhs == 1 ? block12_typed<BK, half_t, true>(geo, links12, tclov, kappa, in, out, nrhs, st)
+                     : block12_typed<BK, half_t, false>(geo, links12, tclov, kappa, in, out, nrhs, st);
 }
 
 }  // namespace
