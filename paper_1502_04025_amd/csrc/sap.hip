@@ -53,6 +53,8 @@
 //
 // Clover input X per rhs: X = kappa T on even sites (A_e = 1 + X) and
 // X = A_o^-1 - 1 on odd sites (A_o^-1 = 1 + X).
+#include <limits>
+
 #include "blockgeo.hpp"
 #include "kernels.hpp"
 #include "lanes.hpp"
@@ -995,11 +997,15 @@ void sap_kernel(SapArgs<S, SS, P> a) {
             pp = fmac(Q[2 * k + 1], Q[2 * k + 1], pp);
         }
         block_sum3<BK, R>(pr_re, pr_im, pp, red);
+        // alpha = <p, r> / <p, p> with one division for both parts. Far from a point source <p, p>
+        // can be so small that its reciprocal overflows: both products are scaled first then, by a
+        // power of two, so that every other quotient keeps its bits.
         R ar = 0, ai = 0;
         if (pp > 0) {
-            const R inv = (R)1 / pp;  // one division for both parts
-            ar = pr_re * inv;
-            ai = pr_im * inv;
+            const R up = pp < 4 * std::numeric_limits<R>::min() ? (R)0x1p64 : (R)1;
+            const R inv = (R)1 / (pp * up);
+            ar = pr_re * up * inv;
+            ai = pr_im * up * inv;
         }
         get_own<BK, R>(buf1, ln, H);  // this step's A_o^-1 H_oe r
         const R kr = kappa * ar, ki = kappa * ai;
