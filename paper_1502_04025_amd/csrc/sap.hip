@@ -39,17 +39,25 @@
 // 256 nearly without spills, no wave idles in one half of a hop, and the exchange costs 24
 // register instructions instead of an LDS round trip. Measured per half-sweep (4 MR steps)
 // against the one-thread-per-pair and one-thread-per-site kernels this replaced:
-//   4^4 lattice, 2^4 domains, FP64, 1 rhs        74.8 -> 28.0 us
-//   16^3 x 32, 8x4^3, FP32 / FP64, 1 rhs         68.8 -> 42.3 us / 442 -> 85.5 us
-//   24^3 x 48, 4^4, FP16, 5 rhs                   564 -> 430 us
-//   32^3 x 64, 8x4^3, FP16, 12 rhs               3860 -> 3153 us
-//   32^3 x 64, 8x4^3, FP32, 4 rhs                2187 -> 1262 us
+//   4^4 lattice, 2^4 domains, FP64, 1 rhs        74.8 -> 29.1 us
+//   16^3 x 32, 8x4^3, FP32 / FP64, 1 rhs         68.8 -> 43.3 us / 442 -> 90.8 us
+//   24^3 x 48, 4^4, FP16, 5 rhs                   564 -> 419 us
+//   32^3 x 64, 8x4^3, FP16, 12 rhs               3860 -> 3097 us
+//   32^3 x 64, 8x4^3, FP32, 4 rhs                2187 -> 1330 us
 // At 32^3 x 64, 12 rhs the FP16 kernel issues 7970 vector instructions per wave and is
 // issuing them 88% of the time.
 //
-// delta_o = A_o^-1 rho_o + kappa sum_i alpha_i A_o^-1 H_oe r_i is accumulated during the
-// MR steps from the vectors A_o^-1 H_oe r_i they form anyway: no closing hop and clover
-// product are needed.
+// Odd sites (ODD_LAST in the kernel). With FP32 and FP64 links delta_o is formed once, from the
+// final delta_e, by a closing hop and clover product. With FP16 links
+// delta_o = A_o^-1 rho_o + kappa sum_i alpha_i A_o^-1 H_oe r_i is accumulated during the MR steps
+// from the vectors A_o^-1 H_oe r_i they form anyway. The sum rounds delta_o in every step, which
+// doubles its error (the next half-sweep takes the odd residual as zero). Relative error of a
+// whole sweep and time of a call of 16 half-sweeps, 16^3 x 32, 8x4^3, accumulated / formed once:
+//   FP64 (8^4, 4^4) 2.24e-16 / 2.09e-16, 1396 / 1506 us
+//   FP32 1.221e-7 / 1.150e-7, 714 / 748 us
+//   FP16 links, FP16 spinors 1.111e-4 / 1.111e-4, 712 / 761 us
+//   FP16 links, FP32 spinors 9.840e-5 / 9.840e-5, 720 / 765 us
+// The rounding of FP16 links hides the sum's, so there the cheaper form stays.
 //
 // Clover input X per rhs: X = kappa T on even sites (A_e = 1 + X) and
 // X = A_o^-1 - 1 on odd sites (A_o^-1 = 1 + X).
@@ -685,8 +693,8 @@ __device__ __forceinline__ R face_hop(const SapArgs<S, SS, P> &a, int64_t b, int
 // backward the upper). Each direction takes whole waves, so a wave runs one direction's
 // code for 32 sites a half; hopping where the sites sit instead would run all four
 // directions in every wave with a quarter (an eighth in x) of its lanes (32^3 x 64, FP16,
-// 12 rhs: 9070 against 7970 instructions per wave, 3270 against 3153 us on 8x4^3 and 3159
-// against 3015 us on 4^4 blocks).
+// 12 rhs: 9070 against 7970 instructions per wave, 3270 against 3097 us on 8x4^3 and 3158
+// against 2936 us on 4^4 blocks).
 template <class BK> struct Faces {
     static constexpr int ext(int mu) { return BK::ext(mu); }
     static constexpr int count(int mu) { return BK::Vbh / BK::ext(mu); }
@@ -846,13 +854,16 @@ template <class BK, class R> __device__ __forceinline__ void block_sum3(R &a, R 
 // link ahead. WIDE chooses between two forms of the FP32 kernel on 8x4^3 blocks, whose
 // workgroups have two waves per SIMD: one workgroup per CU with the look-ahead in 140
 // registers, or two without it in 128. Half-sweep times in us, wide / narrow:
-//   16^3 x 32, 1 rhs (128 workgroups)    42.3 / 46.6
-//   16^3 x 32, 12 rhs (1536)              256 / 234
-//   32^3 x 64, 4 rhs (8192)              1344 / 1262
+//   16^3 x 32, 1 rhs (128 workgroups)    43.2 / 48.9
+//   16^3 x 32, 2 rhs (256)               48.9 / 53.1
+//   16^3 x 32, 3 rhs (384)               80.9 / 72.9
+//   16^3 x 32, 12 rhs (1536)              262 / 239
+//   32^3 x 64, 4 rhs (8192)              1400 / 1333
 // On 4^4 blocks (one wave per SIMD and workgroup) the look-ahead in 140 registers wins
-// throughout (32^3 x 64, 4 rhs: 1216 / 1242); FP16 links need 128 registers either way;
-// FP64 spills less without it (16^3 x 32: 93.3 -> 85.5 us). The forms differ in register
-// use only, not in any operation, so a right-hand side gets the same bits from both.
+// throughout (16^3 x 32, 1 rhs: 39.7 / 44.9; 32^3 x 64, 4 rhs: 1267 / 1320); FP16 links need 128
+// registers either way; FP64 is faster without it (16^3 x 32, 8x4^3: 90.6 against 92.7 us with;
+// 32^3 x 64, 4^4, 2 rhs: 1584 against 1621). The forms differ in register use only, not in any
+// operation, so a right-hand side gets the same bits from both.
 template <class BK, class S, class R> constexpr bool sap_two_forms() {
     return sizeof(S) == 4 && sizeof(R) == 4 && BK::Vbh == 256;
 }
@@ -872,6 +883,7 @@ __global__ __launch_bounds__((Tile<BK, R>::NT)) __attribute__((amdgpu_waves_per_
 void sap_kernel(SapArgs<S, SS, P> a) {
     constexpr int Vbh = BK::Vbh;
     constexpr bool AHEAD = sap_look_ahead<BK, S, R, WIDE>();
+    constexpr bool ODD_LAST = !Storage<S>::scaled;
     typedef Tile<BK, R> T;
     typedef typename T::VR VR;
     __shared__ VR lds[2 * T::BUF];
@@ -917,7 +929,7 @@ void sap_kernel(SapArgs<S, SS, P> a) {
     float *rr_sc = a.rres_sc ? a.rres_sc + (int64_t)rhs * (V / 2) : nullptr;
 
     // own chirality of: A = even rho, then the MR residual r; B = MR solution x; O = odd
-    // rho, then delta_o; H, Q scratch
+    // rho (ODD_LAST: to the end of the MR steps), then delta_o; H, Q scratch
     R A[12], B[12], O[12], H[12], Q[12];
 
     // ---- 1. block residual rho (even into A, odd into O)
@@ -952,14 +964,16 @@ void sap_kernel(SapArgs<S, SS, P> a) {
         }
     }
 
-    // ---- 2. O = A_o^-1 rho_o, bhat_e = rho_e + kappa H_eo A_o^-1 rho_o
+    // ---- 2. Q = A_o^-1 rho_o, bhat_e = rho_e + kappa H_eo A_o^-1 rho_o
     bv.template clover<1>(ln, O, Q);
+    if constexpr (!ODD_LAST) {
 #pragma unroll
-    for (int k = 0; k < 12; ++k) O[k] = Q[k];
+        for (int k = 0; k < 12; ++k) O[k] = Q[k];
+    }
     HopLink<0, 0, BK, S, R> le;
     HopLink<1, 0, BK, S, R> lo;
     le.load(bv, ln);
-    put<BK, R>(buf1, ln, O);
+    put<BK, R>(buf1, ln, Q);
     __syncthreads();
     block_hop_half<0, AHEAD>(le, bv, ln, buf1, H);
 #pragma unroll
@@ -1007,23 +1021,39 @@ void sap_kernel(SapArgs<S, SS, P> a) {
             ar = pr_re * up * inv;
             ai = pr_im * up * inv;
         }
-        get_own<BK, R>(buf1, ln, H);  // this step's A_o^-1 H_oe r
-        const R kr = kappa * ar, ki = kappa * ai;
+        if constexpr (!ODD_LAST) {
+            get_own<BK, R>(buf1, ln, H);  // this step's A_o^-1 H_oe r
+            const R kr = kappa * ar, ki = kappa * ai;
+#pragma unroll
+            for (int k = 0; k < 6; ++k) {
+                const R tr = H[2 * k], ti = H[2 * k + 1];
+                O[2 * k] = fmac(kr, tr, fmac(-ki, ti, O[2 * k]));
+                O[2 * k + 1] = fmac(kr, ti, fmac(ki, tr, O[2 * k + 1]));
+            }
+        }
 #pragma unroll
         for (int k = 0; k < 6; ++k) {
             const R rr_ = A[2 * k], ri = A[2 * k + 1];
             const R qr = Q[2 * k], qi = Q[2 * k + 1];
-            const R tr = H[2 * k], ti = H[2 * k + 1];
             B[2 * k] = fmac(ar, rr_, fmac(-ai, ri, B[2 * k]));
             B[2 * k + 1] = fmac(ar, ri, fmac(ai, rr_, B[2 * k + 1]));
-            O[2 * k] = fmac(kr, tr, fmac(-ki, ti, O[2 * k]));
-            O[2 * k + 1] = fmac(kr, ti, fmac(ki, tr, O[2 * k + 1]));
             A[2 * k] = fmac(-ar, qr, fmac(ai, qi, rr_));
             A[2 * k + 1] = fmac(-ar, qi, fmac(-ai, qr, ri));
         }
     }
 
-    // ---- 4. outputs: psi += delta (even B, odd O), keep delta and the even-site residual
+    // ---- 4. delta_o = A_o^-1 (rho_o + kappa H_oe delta_e)
+    if constexpr (ODD_LAST) {
+        lo.load(bv, ln);
+        put<BK, R>(buf0, ln, B);  // last read before the last two barriers
+        __syncthreads();
+        block_hop_half<1, AHEAD>(lo, bv, ln, buf0, H);
+#pragma unroll
+        for (int k = 0; k < 12; ++k) H[k] = fmac(kappa, H[k], O[k]);
+        bv.template clover<1>(ln, H, O);
+    }
+
+    // ---- 5. outputs: psi += delta (even B, odd O), keep delta and the even-site residual
     R old[12];
     if (a.mode == 2) {
         load_half<R, P>(ps, nullptr, 2 * b, ln.s, ln.f, Vbh, H);

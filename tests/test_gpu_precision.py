@@ -10,6 +10,7 @@ import pytest
 
 import synthetic
 from oracle import lattice as lat
+from oracle.gamma import GAMMA
 
 pytestmark = pytest.mark.gpu
 
@@ -77,3 +78,46 @@ def test_clover_inverse(ctx, block):
         err = [float(np.linalg.norm((x - exact).astype(np.complex128))) for x in (got[:, s, s], gauss_jordan(a))]
         print(f"{block} chirality {k}: device {err[0]:.4e} numpy {err[1]:.4e}", flush=True)
         assert err[0] <= SLACK * err[1]
+
+
+def odd_from_even(u, eta, kappa, psi, block, dtype):
+    """eta + kappa (hops from other blocks) + kappa (hops inside the block) of psi, in dtype."""
+    dims = lat.dims_of(eta)
+    u, psi, out = u.astype(dtype), psi.astype(dtype), eta.astype(dtype)
+    for inside in (False, True):
+        h = np.zeros_like(out)
+        for mu in range(4):
+            g, um = GAMMA[mu].astype(dtype), u[..., mu, :, :]
+            for back in (False, True):
+                chi = lat.shift_bwd(psi, mu, True) if back else lat.shift_fwd(psi, mu, True)
+                gchi = (g[:, :, None] * chi[..., None, :, :]).sum(axis=-2)  # one entry a row: exact
+                half = chi + gchi if back else chi - gchi
+                v = np.conj(np.swapaxes(lat.shift_bwd(um, mu), -1, -2)) if back else um
+                hop = np.einsum("...ab,...sb->...sa", v, half)
+                keep = (lat.internal_bwd if back else lat.internal_fwd)(dims, block, mu) == inside
+                h = h + hop * keep[..., None, None].astype(dtype)
+        out = out + dtype(kappa) * h
+    return out
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("dims,block", [((8, 8, 8, 8), (2, 2, 2, 2)), ((8, 8, 8, 8), (4, 4, 4, 4)),
+                                        ((16, 8, 8, 8), (8, 4, 4, 4))])
+def test_odd_correction_follows_the_even_one(ctx, dims, block, prec):
+    """After one cycle the odd sites of the second colour solve their own equation exactly, given
+    psi on the even sites; without a clover term it reads psi_o = eta_o + kappa H psi_e. Links,
+    source and kappa are FP32 numbers, so the arithmetic alone makes the error."""
+    kappa = 0.125
+    low, high = (np.complex64, np.complex128) if prec == "f32" else (np.complex128, np.clongdouble)
+    u = synthetic.gauge_field(dims, 0.3, 103).astype(np.complex64).astype(np.complex128)
+    eta = synthetic.gaussian_source(dims, 1, 104)[0].astype(np.complex64).astype(np.complex128)
+    f = ctx.load_gauge(u, block)
+    f.compute_clover(0.0)
+    psi = f.sap(kappa, eta, nmr=6, ncy=1, prec=prec)
+    f.free()
+    at = (lat.parity(dims) == 1) & (lat.block_colour(dims, block) == 1)
+    exact = odd_from_even(u, eta, kappa, psi, block, high)[at]
+    plain = odd_from_even(u, eta, kappa, psi, block, low)[at]
+    err = [float(np.sqrt((np.abs(x - exact) ** 2).sum())) for x in (psi[at], plain)]
+    print(f"{block} {prec}: device {err[0]:.4e} numpy {err[1]:.4e}", flush=True)
+    assert err[0] <= SLACK * err[1]
