@@ -484,6 +484,21 @@ template <class S, int VS> struct CloverHalf {
         for (int q = 0; q < 36 / W; ++q) load_dwords<4>(v, o, q * VS, d + 4 * q);
     }
     template <class R> __device__ __forceinline__ R at(int k) const { return (R)as_real(d + DW * k, (S)0); }
+    // To and from LDS: this thread's vectors, nt threads apart.
+    __device__ __forceinline__ void put(u32x4 *lds, int nt) const {
+#pragma unroll
+        for (int q = 0; q < 9 * DW; ++q) lds[q * nt + threadIdx.x] = u32x4{d[4 * q], d[4 * q + 1], d[4 * q + 2], d[4 * q + 3]};
+    }
+    __device__ __forceinline__ void get(const u32x4 *lds, int nt) {
+        int t = threadIdx.x;
+        asm volatile("" : "+v"(t));  // read where it is used, not kept in registers across the MR loop
+#pragma unroll
+        for (int q = 0; q < 9 * DW; ++q) {
+            const u32x4 x = lds[q * nt + t];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) d[4 * q + k] = x[k];
+        }
+    }
 };
 template <int VS> struct CloverHalf<half_t, VS> {
     unsigned d[18];
@@ -852,28 +867,43 @@ template <class BK, class R> __device__ __forceinline__ void block_sum3(R &a, R 
 
 // Waves per SIMD the kernel is compiled for, and whether a hop loads the next direction's
 // link ahead. WIDE chooses between two forms of the FP32 kernel on 8x4^3 blocks, whose
-// workgroups have two waves per SIMD: one workgroup per CU with the look-ahead in 140
-// registers, or two without it in 128. Half-sweep times in us, wide / narrow:
-//   16^3 x 32, 1 rhs (128 workgroups)    43.2 / 48.9
-//   16^3 x 32, 2 rhs (256)               48.9 / 53.1
-//   16^3 x 32, 3 rhs (384)               80.9 / 72.9
-//   16^3 x 32, 12 rhs (1536)              262 / 239
-//   32^3 x 64, 4 rhs (8192)              1400 / 1333
-// On 4^4 blocks (one wave per SIMD and workgroup) the look-ahead in 140 registers wins
-// throughout (16^3 x 32, 1 rhs: 39.7 / 44.9; 32^3 x 64, 4 rhs: 1267 / 1320); FP16 links need 128
-// registers either way; FP64 is faster without it (16^3 x 32, 8x4^3: 90.6 against 92.7 us with;
-// 32^3 x 64, 4^4, 2 rhs: 1584 against 1621). The forms differ in register use only, not in any
-// operation, so a right-hand side gets the same bits from both.
+// workgroups have two waves per SIMD: one workgroup per CU with the look-ahead and, in LDS, the
+// even sites' clover, or two without them in 128 registers. One workgroup per CU leaves fewer
+// blocks to an XCD's L2, which counts when each is used by one or two right-hand sides only.
+// Half-sweep times in us, wide / narrow:
+//   16^3 x 32, 1 rhs (128 workgroups)    43.1 / 48.9     2 rhs  48.5 / 53.1     3 rhs  80.9 / 72.9
+//   16 x 24^2 x 32, 1 rhs (288)         108.7 / 117.7    2 rhs 136.0 / 137.9    4 rhs   218 / 200
+//   32^3 x 64, 1 rhs (2048)               621 / 777      2 rhs   756 / 820      3 rhs  1075 / 1048
+//   48 x 32^2 x 64, 1 rhs (3072)          931 / 1169     2 rhs  1124 / 1233     4 rhs       / 1967
+// (The wide form without the clover in LDS: 42.6, 123.7, 721 and 1075 us with one right-hand side,
+// 745 at 32^3 x 64 with two.) On 4^4 blocks (one wave per SIMD and workgroup) the look-ahead
+// in 140 registers wins throughout (16^3 x 32, 1 rhs: 39.7 / 44.9; 32^3 x 64, 4 rhs: 1267 / 1320);
+// FP16 links need 128 registers either way; FP64 is faster without it (16^3 x 32, 8x4^3: 90.6 against
+// 92.7 us with; 32^3 x 64, 4^4, 2 rhs: 1584 against 1621). The forms differ in where operands
+// wait, not in any operation, so a right-hand side gets the same bits from both.
 template <class BK, class S, class R> constexpr bool sap_two_forms() {
     return sizeof(S) == 4 && sizeof(R) == 4 && BK::Vbh == 256;
 }
 template <class BK, class S, class R, bool WIDE> constexpr int sap_waves_per_eu() {
     if (BK::Vbh < 32) return sizeof(R) == 8 ? 1 : 2;  // 2^4 blocks: one wave per workgroup
-    if (sizeof(R) == 8) return 2;
+    if (sizeof(R) == 8 || (WIDE && sap_two_forms<BK, S, R>())) return 2;
     return sizeof(S) == 4 && WIDE ? 3 : 4;
 }
 template <class BK, class S, class R, bool WIDE> constexpr bool sap_look_ahead() {
     return sizeof(R) == 4 && (WIDE || !sap_two_forms<BK, S, R>());
+}
+// LDS to request beside the kernel's own. A single right-hand side with FP32 links on 4^4 blocks
+// re-reads each block's 147 KB from the L2 in every MR step: with three workgroups per CU the 96
+// blocks of an XCD miss its 4 MB and the fabric's rate counts. Where there are two workgroups per
+// CU or more, they then get a CU each in turn. Half-sweep times in us, three per CU / one:
+//   16^2 x 24 x 32 (384 workgroups)  61.0 / 68.7    16^2 x 32^2 (512)   97.2 / 76.8
+//   16 x 24^2 x 32 (576)              116 / 102     24^3 x 48 (1296)     265 / 214
+//   32^3 x 64 (4096)                  769 / 575     48^3 x 64 (13824)   2633 / 1888
+// With two right-hand sides per block it loses (32^3 x 64: 761 / 1010), on FP16 it is not needed.
+template <class BK, class S, class R> int sap_extra_lds(int nact, int64_t nwg) {
+    constexpr int own = 2 * Tile<BK, R>::BUF * 16;
+    if (sizeof(S) == 4 && sizeof(R) == 4 && BK::Vbh == 128 && nact == 1 && nwg >= 512) return 84 * 1024 - own;
+    return 0;
 }
 
 }  // namespace
@@ -888,6 +918,8 @@ void sap_kernel(SapArgs<S, SS, P> a) {
     typedef typename T::VR VR;
     __shared__ VR lds[2 * T::BUF];
     __shared__ __align__(16) R red[3 * T::NW];
+    constexpr bool XL = WIDE && sap_two_forms<BK, S, R>();
+    __shared__ u32x4 xl[XL ? 9 * T::NT : 1];  // each thread's half of its even site's clover
     VR *buf0 = lds, *buf1 = lds + T::BUF;  // even-site vectors r, odd-site vectors
 
     const Geom &geo = a.geo;
@@ -931,6 +963,12 @@ void sap_kernel(SapArgs<S, SS, P> a) {
     // own chirality of: A = even rho, then the MR residual r; B = MR solution x; O = odd
     // rho (ODD_LAST: to the end of the MR steps), then delta_o; H, Q scratch
     R A[12], B[12], O[12], H[12], Q[12];
+
+    if constexpr (XL) {
+        CloverHalf<S, BlockView<BK, S, R>::VS> c;
+        c.load(bv.X, bv.off(0, ln.s), ln.f);
+        c.put(xl, T::NT);
+    }
 
     // ---- 1. block residual rho (even into A, odd into O)
     if (a.mode < 2) {
@@ -997,7 +1035,13 @@ void sap_kernel(SapArgs<S, SS, P> a) {
         put<BK, R>(buf1, ln, Q);
         __syncthreads();
         block_hop_half<0, AHEAD>(le, bv, ln, buf1, H);  // even: H_eo Q
-        bv.template clover<0>(ln, A, Q);         // even: A_e r, then p = A_e r - kappa^2 H
+        if constexpr (XL) {                      // even: A_e r, then p = A_e r - kappa^2 H
+            CloverHalf<S, BlockView<BK, S, R>::VS> c;
+            c.get(xl, T::NT);
+            clover_half_mul(c, A, Q, (R)1);
+        } else {
+            bv.template clover<0>(ln, A, Q);
+        }
         R pr_re = 0, pr_im = 0, pp = 0;
 #pragma unroll
         for (int k = 0; k < 12; ++k) Q[k] = fmac(-k2, H[k], Q[k]);
@@ -1105,12 +1149,13 @@ static hipError_t sap_typed(const Geom &geo, const SapArgsHost &h, int colour, i
     const int64_t nblk = geo.Nd / 2, nwg = nblk * h.nact / T::PER;
     if (nblk % 8 != 0 || nwg > 0x7fffffff) return hipErrorInvalidValue;
     if constexpr (sap_two_forms<BK, S, R>()) {
-        if (nwg > 256) {  // more than one workgroup per CU
+        if (nwg > 256 && h.nact > 2) {  // more than one workgroup per CU, and blocks shared by three or more
             hipLaunchKernelGGL((sap_kernel<BK, S, SS, R, P, false>), dim3((unsigned)nwg), dim3(T::NT), 0, st, a);
             return hipGetLastError();
         }
     }
-    hipLaunchKernelGGL((sap_kernel<BK, S, SS, R, P, true>), dim3((unsigned)nwg), dim3(T::NT), 0, st, a);
+    hipLaunchKernelGGL((sap_kernel<BK, S, SS, R, P, true>), dim3((unsigned)nwg), dim3(T::NT),
+                       (sap_extra_lds<BK, S, R>(h.nact, nwg)), st, a);
     return hipGetLastError();
 }
 
