@@ -167,7 +167,8 @@ int sapdd_free_field(sapdd_ctx *ctx, sapdd_field *field);
  * complex128, host or device per flags), with links, clover and spinors held in storage
  * precision `prec` (arithmetic in FP64 for SAPDD_F64, FP32 otherwise; SAPDD_F16 stores
  * every site with one FP32 scale, the half-precision storage of Sec. 3.3). in and out
- * may not overlap; the caller owns both. EINVAL for nrhs < 1, a bad precision or a null
+ * may be the same array or overlap (the library then reads in from a copy where it has to);
+ * the caller owns both. EINVAL for nrhs < 1, a bad precision or a null
  * argument; ENOMEM if a workspace cannot be allocated. */
 int sapdd_apply_D(sapdd_ctx *ctx, const sapdd_field *field, double kappa, int prec, int nrhs,
                   const double *in, double *out, int flags);

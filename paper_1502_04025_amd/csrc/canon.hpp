@@ -60,7 +60,8 @@ template <class S, class R> __device__ __forceinline__ void round_site(const dou
 }
 
 // A site's slot in LDS: 12 complex components in storage precision S, its canonical index
-// and, for FP16, its scale. The strides spread neighbouring slots over the banks.
+// and, for FP16, its scale. The FP64 and FP32 strides (208 and 104 bytes) spread neighbouring
+// slots over the banks; the FP16 slot has 64 bytes, so that every fourth starts on the same bank.
 template <class S> struct CanonSlot;
 template <> struct CanonSlot<double> {
     typedef double v2 __attribute__((ext_vector_type(2)));

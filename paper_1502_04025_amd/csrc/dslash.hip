@@ -64,8 +64,9 @@ template <class BK> constexpr int full_chunks_per_block() {
 // How blocks go to the XCDs. In eight contiguous ranges, the next blocks in x (and y) are on
 // the same XCD at about the same time and the face spinors come from its L2, as long as few
 // right-hand sides lie between them; with many, a block's own right-hand sides fill the L2
-// and dealing the blocks out one by one keeps the fabric's traffic even. FP64 operator in
-// us, one by one / ranges:
+// and dealing the blocks out one by one keeps the fabric's traffic even. Ranges gain 7 to 16% for
+// one right-hand side and 1 to 10% for two to four; from five on they gain 1% on small lattices
+// and lose 2 to 5% on large ones. FP64 operator in us, one by one / ranges:
 //   16^3 x 32, 8x4^3, 1 rhs     56.0 / 46.9     4 rhs   123 / 118    8 rhs   234 / 231
 //   24^3 x 48, 4^4, 2 rhs        393 / 355      5 rhs   775 / 766
 //   32^3 x 64, 8x4^3, 1 rhs      848 / 746      6 rhs  2720 / 2845   12 rhs  5290 / 5400
@@ -80,13 +81,14 @@ static bool dslash_xcd_ranges(int nact) { return nact <= 4; }
 // wave per SIMD gained nothing. Operator alone, global / tile, in us:
 //   16^3 x 32, 8x4^3, 1 rhs      FP64 52.2 / 47.2, FP32 25.3 / 24.7
 //   24^3 x 48, 4^4, 5 rhs        FP64 966 / 772, FP32 545 / 448
-//   32^3 x 64, 8x4^3, 6 rhs      FP64 3640 / 2810, FP32 2150 / 1600
+//   32^3 x 64, 8x4^3, 6 rhs      FP64 3640 / 2720, FP32 2150 / 1600
 //   32^3 x 64, 4^4, 12 rhs       FP64 6450 / 5170, FP32 3840 / 3150
 //   48^3 x 96, 8x4^3, 2 rhs      FP64 6770 / 5500, FP32 3690 / 2990
 // On 2^4 blocks half of all hops leave the block: they keep the reads from global memory. So
-// do FP16 spinors, which would gain as much, because the compiler fuses their site scale into
-// the projection in another order behind the tile's branches, and the rounding to FP16
-// storage would then give other results than before.
+// do FP16 spinors, not for speed (they would gain as much): behind the tile's branches the
+// compiler fuses their site scale into the projection in another order, and the rounding to
+// FP16 storage then gives other results. It would take a projection of explicit FMAs in the
+// present order.
 template <class BK, class TI, bool CIN> struct SpinorTile {
     static constexpr bool ON = BK::Vbh % (DSLASH_WG / 2) == 0 && !Storage<TI>::scaled;
     static constexpr int W = Vec<TI>::W, NV = 24 / W, H = DSLASH_WG / 2;
@@ -282,9 +284,9 @@ __global__ __launch_bounds__(DSLASH_WG) void dslash_full_kernel(Geom geo, CF<S> 
         }
         if constexpr (CANON) {
             // The operator API's result goes to the caller's array from here: against a pass
-            // of its own the calls are 2 to 15% faster (32^3 x 64, 8x4^3, 4 rhs, FP64
-            // 3568 -> 3079 us, FP32 2078 -> 1903 us, FP16 1524 -> 1493 us; 16^3 x 32, 1 rhs, FP64
-            // 80.7 -> 73.5 us).
+            // of its own the calls were 2 to 15% faster, with spinors still read from global
+            // memory and packed first (32^3 x 64, 8x4^3, 4 rhs, FP64 3568 -> 3079 us, FP32 2078 ->
+            // 1903 us, FP16 1524 -> 1493 us; 16^3 x 32, 1 rhs, FP64 80.7 -> 73.5 us).
             // slots in canonical order where the chunk holds both parities of its blocks
             int n = threadIdx.x;
             if constexpr (ST::ON) n = canon_slot_of<BK>(x) - 2 * s0;

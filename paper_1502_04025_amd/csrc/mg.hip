@@ -671,8 +671,8 @@ __device__ __forceinline__ int64_t coarse_entry_row(const MgGmres &G, int e) {
 // vectors pass through LDS in FP64; wave n sums the column groups' parts of system n, which
 // all threads read back for their dot products. Bound by latency (one pass of a few dependent
 // loads and three barriers) and by the stencil's 19 MB from L2. The sums of a system do not
-// depend on NS or on the other systems. 16^3 x 32, 8x4^3
-// aggregates, K = 32, 4 systems: 16.4 us with a workgroup per system, 8.9 us.
+// depend on NS or on the other systems. 16^3 x 32, 8x4^3 aggregates, K = 32: 6.0, 6.9 and 8.9 us for
+// 1, 2 and 4 systems (16.4 us for 4 with a workgroup per system), 13.5 us for 5.
 template <int NS>
 __global__ __launch_bounds__(MG_AWG) __attribute__((amdgpu_waves_per_eu(1, 2))) void mg_capply_kernel(MgGmres G,
                                                                                                       int j, int nact) {
@@ -1174,7 +1174,9 @@ static void launch_arnoldi(bool tail, int j, dim3 ga, hipStream_t st, const MgGm
 }
 
 // Step j of the operator kernel. Four systems share a workgroup's stencil entries, so that one
-// pass over the stencil serves them.
+// pass over the stencil serves them. The last group may be smaller: its workgroups compute its last
+// system up to four times and store it once (5 systems: 13.5 us), and three systems take the form
+// for four.
 static void launch_capply(const MgGmres &G, int nact, int j, hipStream_t st) {
     const int ns = nact >= 3 ? 4 : nact;
     const dim3 g((unsigned)G.nwa, (unsigned)((nact + ns - 1) / ns));
